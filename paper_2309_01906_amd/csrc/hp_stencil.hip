@@ -2,7 +2,7 @@
 // algorithms, section 2, and its ghost surfaces, section 4): `steps` five-point
 // Jacobi sweeps of a 2-D float array with fixed boundary cells,
 //   B[i][j] = c0 A[i][j] + c1 ((A[i-1][j] + A[i+1][j]) + (A[i][j-1] + A[i][j+1])).
-// The tiling is repeated on the levels that have local memory: each workgroup owns a
+// Two forms.  In LDS the tiling is repeated on the levels that have local memory: each workgroup owns a
 // TH x 64 output tile in LDS (the workgroup level), each lane a column strip of 4
 // cells in registers (the lane level).  A launch reads the tile plus a ghost surface
 // T cells wide into LDS once, runs T sweeps there -- the valid region shrinks by one
@@ -11,7 +11,10 @@
 // bands, so that the ghost cells neighbouring tiles share come from HBM once into
 // the XCD's L2 (the X level's shared cache).  The plan checks the tile against the
 // workgroup level's local memory in the level-property table; more sweeps than one
-// launch holds run as several launches through a buffer the plan owns.
+// launch holds run as several launches through a buffer the plan owns.  In registers
+// (below) a wave keeps a strip of columns and streams down its rows, the last two rows
+// of every sweep in its lanes; launches of several sweeps take it unless the array is
+// too small (reg_form).
 #include <hip/hip_runtime.h>
 
 #include <new>
@@ -236,6 +239,188 @@ __global__ void __launch_bounds__(threads_of(TH)) k_stencil(const float* __restr
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same sweeps in registers.  A wave owns a strip of kRegCols columns, each lane
+// four neighbouring ones, and walks down its rows; row i of the input gives row i - k
+// of sweep k in the same step, so a lane keeps the last two rows of every sweep (8
+// registers per sweep) and the T sweeps cost no LDS and no barrier.  Left and right
+// neighbours of a lane's outer cells come from the next lanes by DPP wave shifts, so a
+// cell and sweep costs the 6 arithmetic instructions of its formula and a fraction of
+// a row's overhead, where the LDS form pays 3.5 LDS reads, a write and their addresses
+// on top.  Every cell is the same fp32 function of its neighbours as in the LDS form,
+// so the results have the same bits.
+//
+// The ghost surface is 4 or 8 columns on each side (a vector multiple of at least T:
+// 248 or 240 of 256 columns are stored) and T rows above and below.
+constexpr int kRegCols = 4 * kWave;
+constexpr int kRegWaves = 4;  // waves per workgroup (independent strips)
+constexpr int reg_ghost(int t) { return t <= 4 ? 4 : 8; }
+constexpr int kRegAhead = 3;  // input rows in flight per wave
+
+// four columns of a row at any 4-byte alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// the value of the lane below (lane - 1) and above (lane + 1); 0 beyond the wave
+__device__ __forceinline__ float from_left(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, true));  // wave_shr:1
+}
+__device__ __forceinline__ float from_right(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, true));  // wave_shl:1
+}
+
+// One input row through all T sweeps: `d` is row i of the input on entry and row
+// i - T of sweep T on return; up[k] and mid[k] are rows i - k - 2 and i - k - 1 of
+// sweep k.  COLS: cells of `keep` (the array's first and last column) pass through
+// every sweep.  ROWS: the array's first and last row do.
+template <int T, bool COLS, bool ROWS>
+__device__ __forceinline__ f32x4 reg_step(f32x4 d, f32x4* up, f32x4* mid, float c0, float c1, const bool* keep, long long i,
+                                          long long R) {
+#pragma unroll
+  for (int k = 0; k < T; ++k) {
+    const f32x4 u = up[k], m = mid[k];
+    const float l[4] = {from_left(m.w), m.x, m.y, m.z};
+    const float r[4] = {m.y, m.z, m.w, from_right(m.x)};
+    const bool row = ROWS && (i - k - 1 == 0 || i - k - 1 == R - 1);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = c0 * m[e] + c1 * ((u[e] + d[e]) + (l[e] + r[e]));
+      v[e] = (row || (COLS && keep[e])) ? m[e] : x;
+    }
+    up[k] = m;
+    mid[k] = d;
+    d = v;
+  }
+  return d;
+}
+
+// Rows [r0, r1) of the strip whose first column is j0 - G.
+template <int T, bool COLS>
+__device__ __forceinline__ void reg_strip(const float* __restrict__ in, float* __restrict__ out, long long R, long long C,
+                                          long long j0, long long r0, long long r1, float c0, float c1) {
+  constexpr int G = reg_ghost(T);
+  const int lane = (int)(threadIdx.x & 63);
+  const long long j = j0 - G + 4 * lane;  // this lane's first column
+  bool keep[4] = {false, false, false, false};
+  uint32_t col[4];  // COLS: the columns read, inside the array
+  if constexpr (COLS) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const long long c = j + e;
+      keep[e] = c <= 0 || c >= C - 1;  // beyond the array nothing is read by a stored cell
+      col[e] = (uint32_t)(c < 0 ? 0 : (c > C - 1 ? C - 1 : c));
+    }
+  }
+  const uint32_t off = (uint32_t)(4 * lane);
+  auto load = [&](long long i) -> f32x4 {
+    const float* row = in + (i < R ? i : R - 1) * C;
+    if constexpr (COLS) return f32x4{row[col[0]], row[col[1]], row[col[2]], row[col[3]]};
+    else return *reinterpret_cast<const f32x4u*>(row + (j0 - G) + off);
+  };
+  const bool mine = lane >= G / 4 && lane < (kRegCols - G) / 4;
+  auto store = [&](long long i, f32x4 v) {
+    float* row = out + i * C;
+    if constexpr (COLS) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (mine && j + e < C) row[j + e] = v[e];
+    } else {
+      if (mine) __builtin_nontemporal_store(v, reinterpret_cast<f32x4u*>(row + (j0 - G) + off));
+    }
+  };
+  f32x4 up[T], mid[T];
+#pragma unroll
+  for (int k = 0; k < T; ++k) up[k] = mid[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const long long i0 = r0 > T ? r0 - T : 0, i1 = r1 + T;  // input rows, then T steps' flush
+  f32x4 x[kRegAhead];
+#pragma unroll
+  for (int u = 0; u < kRegAhead; ++u) x[u] = load(i0 + u);
+  // kRegAhead steps; a step past the last one reads the last row again and stores nothing
+  auto steps = [&](auto rows_c, long long i) {
+#pragma unroll
+    for (int u = 0; u < kRegAhead; ++u) {
+      const f32x4 d = x[u];
+      x[u] = load(i + u + kRegAhead);
+      const f32x4 v = reg_step<T, COLS, decltype(rows_c)::value>(d, up, mid, c0, c1, keep, i + u, R);
+      const long long o = i + u - T;
+      if (o >= r0 && o < r1) store(o, v);
+    }
+  };
+  long long i = i0;
+  for (; i < i1 && i <= T; i += kRegAhead) steps(std::true_type{}, i);               // row 0 is in flight
+  for (; i < i1 && i + kRegAhead <= R; i += kRegAhead) steps(std::false_type{}, i);
+  for (; i < i1; i += kRegAhead) steps(std::true_type{}, i);                          // row R - 1 is in flight
+}
+
+template <int T>
+__global__ void __launch_bounds__(kRegWaves* kWave) k_stencil_reg(const float* __restrict__ in, float* __restrict__ out,
+                                                                 long long R, long long C, uint32_t nstrips,
+                                                                 uint32_t nblocks, int rows, float c0, float c1) {
+  constexpr int G = reg_ghost(T);
+  const uint32_t wid = stencil_tile(blockIdx.x, gridDim.x, true) * kRegWaves +
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t rb = wid / nstrips, st = wid - rb * nstrips;
+  if (rb >= nblocks) return;
+  const long long j0 = (long long)st * (kRegCols - 2 * G);
+  const long long r0 = (long long)rb * rows, r1 = r0 + rows < R ? r0 + rows : R;
+  if (j0 < G || j0 - G + kRegCols > C - 1) reg_strip<T, true>(in, out, R, C, j0, r0, r1, c0, c1);
+  else reg_strip<T, false>(in, out, R, C, j0, r0, r1, c0, c1);
+}
+
+// Rows per wave: the waves of nb row blocks run as `used` = ceil(waves / SIMDs) shares
+// of rows + 2 T steps on the fullest SIMD.  From 6 sweeps the steps are issue-bound and
+// a wave alone leaves gaps, worth about 0.6 of a share (8192 x 8192, 8 sweeps: 3 shares
+// of 111 steps 148 us, 2 of 158 162 us).  Below that HBM is the bound and few long
+// strips stream best, but at least two waves per SIMD (8192 x 8192, 4 sweeps: 2 shares
+// 122 us, 4 shares 130 us).
+static int reg_rows(long long R, long long C, int t) {
+  const long long simds = 1024;  // 256 compute units x 4
+  const long long w = kRegCols - 2 * reg_ghost(t);
+  const long long ns = (C + w - 1) / w;
+  long long best = 0, rows = R;
+  for (long long k = 1; k <= 8; ++k) {
+    long long nb = k * simds / ns;
+    if (nb < 1) nb = 1;
+    const long long rb = (R + nb - 1) / nb;
+    const long long used = (ns * ((R + rb - 1) / rb) + simds - 1) / simds;
+    const long long cost = (t >= 6 ? 10 * used + 6 : 10 * (used < 2 ? 2 : used)) * (rb + 2 * t);
+    if (best == 0 || cost < best) {
+      best = cost;
+      rows = rb;
+    }
+  }
+  return (int)rows;
+}
+
+// Whether a launch of t sweeps takes the register form.  Measured against the best LDS
+// tile: one sweep stays with LDS (8192 x 8192: 98 against 111 us, both near a copy's
+// rate), two sweeps too on arrays beyond the last-level cache (8192 x 8192: 102 against
+// 110 us; 4096 x 4096: 26 against 24 us) and on narrow ones that fill their strips
+// badly (7000 x 300: 8.0 against 8.6 us); 3 and 4 sweeps are never slower (8192 x 8192,
+// 4: 147 -> 122 us).  From 5 sweeps a small array leaves each wave fewer rows than
+// ghost rows: at 1.5 T rows per wave the forms are equal (1129 x 2496, 8 sweeps: 20.4
+// and 19.5 us), below it LDS is faster (1024 x 1024: 13.5 against 21.5 us), above it
+// registers (8192 x 8192, 8: 265 -> 148 us).
+static bool reg_form(long long R, long long C, int t) {
+  if (t <= 1) return false;
+  if (t == 2) {
+    const long long w = kRegCols - 2 * reg_ghost(2), ns = (C + w - 1) / w;
+    return R < (1ll << 25) / C && 4 * C >= 3 * ns * w;
+  }
+  return t <= 4 || 2 * (long long)reg_rows(R, C, t) >= 3 * t;
+}
+
+template <int T>
+hp_status launch_reg(const float* in, float* out, long long R, long long C, float c0, float c1, hipStream_t st) {
+  constexpr int w = kRegCols - 2 * reg_ghost(T);
+  const int rows = reg_rows(R, C, T);
+  const uint32_t ns = (uint32_t)((C + w - 1) / w), nb = (uint32_t)((R + rows - 1) / rows);
+  const uint32_t grid = (ns * nb + kRegWaves - 1) / kRegWaves;
+  hipLaunchKernelGGL(k_stencil_reg<T>, dim3(grid), dim3(kRegWaves * kWave), 0, st, in, out, R, C, ns, nb, rows, c0, c1);
+  if (hipGetLastError() != hipSuccess) return hp::fail(HP_EDEVICE, "stencil launch failed");
+  return HP_OK;
+}
+
 template <int T, int TH>
 hp_status launch_t(const float* in, float* out, long long R, long long C, bool xcd, float c0, float c1,
                    hipStream_t st) {
@@ -251,6 +436,19 @@ hp_status launch_t(const float* in, float* out, long long R, long long C, bool x
                      off32, vec4, c0, c1);
   if (hipGetLastError() != hipSuccess) return hp::fail(HP_EDEVICE, "stencil launch failed");
   return HP_OK;
+}
+
+static hp_status launch_reg_t(int t, const float* in, float* out, long long R, long long C, float c0, float c1,
+                              hipStream_t st) {
+  switch (t) {
+    case 2: return launch_reg<2>(in, out, R, C, c0, c1, st);
+    case 3: return launch_reg<3>(in, out, R, C, c0, c1, st);
+    case 4: return launch_reg<4>(in, out, R, C, c0, c1, st);
+    case 5: return launch_reg<5>(in, out, R, C, c0, c1, st);
+    case 6: return launch_reg<6>(in, out, R, C, c0, c1, st);
+    case 7: return launch_reg<7>(in, out, R, C, c0, c1, st);
+    default: return launch_reg<8>(in, out, R, C, c0, c1, st);
+  }
 }
 
 template <int TH>
@@ -278,6 +476,7 @@ struct hp_stencil_s {
   float c0, c1;
   int tile_rows;     // output rows per workgroup tile (32 or 64)
   bool xcd;          // tiles dealt to XCDs in bands
+  bool reg;          // no tile asked for: launches may take the register form
   int per_launch;    // sweeps per launch (1..8)
   int launches;      // ceil(steps / per_launch); the last launch takes the remainder
   float* tmp;        // rows x cols buffer for the intermediate launches (null for one launch)
@@ -341,6 +540,7 @@ extern "C" hp_status hp_stencil_plan_ex(int64_t rows, int64_t cols, int32_t step
   s->c1 = c1;
   s->tile_rows = th;
   s->xcd = !(flags & HP_STENCIL_NO_XCD);
+  s->reg = tile_rows == 0 && s->xcd;
   s->per_launch = t;
   s->launches = (steps + t - 1) / t;
   s->tmp = nullptr;
@@ -393,7 +593,8 @@ extern "C" hp_status hp_stencil_run(hp_stencil_t s, const float* d_in, float* d_
   for (int j = 0; j < s->launches; ++j) {
     const int t = left < s->per_launch ? left : s->per_launch;
     float* dst = ((s->launches - 1 - j) % 2 == 0) ? d_out : s->tmp;
-    const hp_status r = s->tile_rows == 64 ? hp::launch_th<64>(t, src, dst, R, C, s->xcd, s->c0, s->c1, st)
+    const hp_status r = s->reg && hp::reg_form(R, C, t) ? hp::launch_reg_t(t, src, dst, R, C, s->c0, s->c1, st)
+                        : s->tile_rows == 64 ? hp::launch_th<64>(t, src, dst, R, C, s->xcd, s->c0, s->c1, st)
                                            : hp::launch_th<32>(t, src, dst, R, C, s->xcd, s->c0, s->c1, st);
     if (r != HP_OK) return r;
     src = dst;

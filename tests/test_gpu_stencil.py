@@ -78,6 +78,27 @@ def test_full_size_8192(steps):
     check_against_oracle(x, got, steps, 0.6, 0.1)
 
 
+@pytest.mark.parametrize("shape,steps", [
+    ((700, 248), 2), ((5, 249), 3), ((333, 497), 4), ((1, 700), 3), ((2, 1000), 4), ((41, 256), 4),  # strips of 248
+    ((2600, 240), 5), ((2600, 241), 6), ((2599, 721), 7), ((2600, 1203), 8), ((2601, 960), 16)])     # strips of 240
+def test_register_strips_agree_with_the_lds_tiles(shape, steps):
+    """Arrays that end at, one before and one after a register strip's last column, and
+    rows at any 4-byte alignment: the same bits as the LDS tiles."""
+    import torch
+    say("case stencil strips", shape, steps)
+    n = shape[0] * shape[1]
+    buf = torch.from_numpy(workloads.normal_f32(133, (n + 1,))).cuda()
+    for off in (0, 1):
+        x = buf[off:off + n].view(shape)
+        with hp.Stencil(*shape, steps, 0.6, 0.1) as a, hp.Stencil(*shape, steps, 0.6, 0.1, tile_rows=32) as b:
+            guard = torch.full((n + 2,), 7.0, device="cuda")
+            got, want = guard[1:n + 1].view(shape), torch.empty_like(x)
+            a.run(x, got)
+            b.run(x, want)
+            assert torch.equal(got, want)
+            assert guard[0] == 7.0 and guard[n + 1] == 7.0
+
+
 def test_stencil_harmonic_field_is_exact():
     i, j = np.mgrid[0:300, 0:400]
     x = (2 * i - 3 * j + 5).astype(np.float32)
