@@ -131,7 +131,7 @@ __device__ __forceinline__ void simple_task(const SimpleDesc& D, uint32_t g, int
     }
     a = lane_combine<T>(a, S, lane);
     if (valid && real && uv1 == 0) {
-      const double v = (double)a.s + (double)a.c;
+      const double v = float_result(a);
       if (D.bits & 0x100u) reinterpret_cast<double*>(D.out)[o] = v;
       else reinterpret_cast<float*>(D.out)[o] = (float)v;
     }

@@ -16,8 +16,8 @@ namespace hp {
 //
 // The fold order is fixed by the partial count G alone, never by how many threads
 // run it, so every launch form of a plan gives the same bits:
-//   floats, G <= kSeqFold: one lane adds s then c of partials 0, 1, ..., G-1 into
-//     an fp64 pair;
+//   floats, G <= kSeqFold: one lane adds partials 0, 1, ..., G-1 into an fp64
+//     (sum, error) pair;
 //   floats, G > kSeqFold: lane k adds partials k, k+64, ... the same way and the 64
 //     pairs merge in a xor butterfly;
 //   integers: the operators are exact, associative and commutative (ARG keeps the
@@ -41,10 +41,7 @@ __device__ __forceinline__ double fold_flt_seq(const char* part, long long G) {
       if (k0 + u < G) v[u] = FloatT<float>::get(part, k0 + u);
 #pragma unroll
     for (int u = 0; u < kFoldBatch; ++u)
-      if (k0 + u < G) {
-        dpair_add(a, (double)v[u].s);
-        dpair_add(a, (double)v[u].c);
-      }
+      if (k0 + u < G) dpair_add(a, v[u]);
   }
   return a.s + a.c;
 }
@@ -60,10 +57,7 @@ __device__ __forceinline__ double fold_flt_wave(const char* part, long long G, i
       if (k0 + (long long)u * kWave < G) v[u] = FloatT<float>::get(part, k0 + (long long)u * kWave);
 #pragma unroll
     for (int u = 0; u < B; ++u)
-      if (k0 + (long long)u * kWave < G) {
-        dpair_add(a, (double)v[u].s);
-        dpair_add(a, (double)v[u].c);
-      }
+      if (k0 + (long long)u * kWave < G) dpair_add(a, v[u]);
   }
 #pragma unroll
   for (int b = 0; b < 6; ++b) {

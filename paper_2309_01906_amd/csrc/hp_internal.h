@@ -21,7 +21,7 @@ namespace hp {
 constexpr int kMaxDepth = HP_MAX_DEPTH;
 constexpr int kWave = 64;
 constexpr int kMaxWaves = 16;
-constexpr int kSlotBytes = 16;  // one LDS / workspace slot: an int carrier {i64 v; i32 idx} or a float pair
+constexpr int kSlotBytes = 16;  // one LDS / workspace slot: an int carrier {i64 v; i32 idx} or an fp64 sum
 
 enum OutKind : int32_t { OUT_I32 = HP_I32, OUT_I64 = HP_I64, OUT_F32 = HP_F32, OUT_F64 = HP_F64 };
 
@@ -120,11 +120,32 @@ struct alignas(16) DevPlan {
   DevSeg seg[kMaxDepth];
 };
 
+// How hp_run launches an automatic plan with one reduction per output over a contiguous
+// block (hp_rows.hip); the level map and the partial count it reports stay the plan's.
+enum RowKind : int32_t { ROWS_OFF = 0, ROWS_TINY, ROWS_SHORT, ROWS_LONG };
+struct RowRoute {
+  int32_t kind;
+  int32_t dtype, op;
+  int32_t f32_out;
+  int64_t n_out;
+  int64_t block;      // elements per output
+  uint32_t grid;      // workgroups
+  int32_t lane_bits;  // short: 2^lane_bits lanes per output
+  int32_t vecs;       // short: vectors per lane (1 to 4)
+  int32_t ahead;      // short: steps in flight
+  int32_t waves;      // long: waves per workgroup
+  uint32_t parts;     // long: workgroups per output
+  int64_t part_len;   // long: elements per workgroup (the last may have fewer)
+};
+
 // Host-side result of planning (no device resources).
 struct Lowered {
   DevPlan dp;
   hp_plan_info info;
 };
+
+// The row route of a nest that `lower` planned into L (kind ROWS_OFF: none).
+RowRoute row_route(const hp_nest* nest, const hp_level_map* map, uint32_t flags, const Lowered& L);
 
 // Fill `out` from nest + map; sets the thread-local error text on failure.
 // force_nw > 0 (batched plans): the plan must use exactly that many waves per

@@ -21,9 +21,12 @@
 //   workgroups  a partial per workgroup in global memory; a second, small kernel
 //               folds each output's partials in index order (the grid has no
 //               barrier across its units, sections 1 and 3.2).
-// Float sums keep an fp32 (sum, error) pair per lane, extended by TwoSum for every
-// element, and use fp64 only when partials of several workgroups are folded and for
-// the output.
+// Float sums are kept in fp64 from the first element on.  gfx950 widens and adds in
+// fp64 at the rate of plain fp32 (measured: v_cvt_f64_f32 5.2 and v_add_f64 4.9 cycles
+// per wave against 4.2 for v_add_f32), so an fp32 element costs 2 VALU instructions
+// where an fp32 (sum, error) pair extended by TwoSum costs 7, a bf16 element 3 where
+// the pair costs 8, and the rounding of a sum of n elements is bounded by n 2^-53
+// sum|a| where the pair's error word gave n 2^-48 sum|a|.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -95,9 +98,7 @@ __device__ __forceinline__ uint32_t g_digit(uint32_t g, const DevLevel& L) {
 // ---------------------------------------------------------------------------
 // carriers
 
-struct FAcc {
-  float s, c;  // value = s + c; c collects the exact rounding errors of s
-};
+typedef double FAcc;  // float sums
 struct IAcc {
   long long v;
   int i;  // ARG levels: iteration index of v
@@ -110,36 +111,15 @@ struct FloatT {
   using Acc = FAcc;
   static constexpr bool kFloat = true;
   static constexpr bool kKey = false;
-  __device__ static __forceinline__ Acc identity(int) { return Acc{0.f, 0.f}; }
-  // TwoSum per element, its exact error added to c.  (Kahan's four-operation step
-  // rounds x + c before it adds, which loses about u |x| per element: on a 2^20-element
-  // sum of N(0,1) values that is 2e-6 relative to the result, above the 1e-6 rule.)
-  __device__ static __forceinline__ void add(Acc& a, float x, long long, int) {
-    float s, e;
-    two_sum(a.s, x, s, e);
-    a.s = s;
-    a.c += e;
-  }
+  __device__ static __forceinline__ Acc identity(int) { return 0.0; }
+  __device__ static __forceinline__ void add(Acc& a, float x) { a += (double)x; }
   // symmetric in (a, b), so both partners of a butterfly step get identical bits
-  __device__ static __forceinline__ Acc merge(Acc a, Acc b, int) {
-    float s, e;
-    two_sum(a.s, b.s, s, e);
-    const float c = (a.c + b.c) + e;
-    const float s2 = s + c;
-    return Acc{s2, c - (s2 - s)};
-  }
-  __device__ static __forceinline__ Acc shfl(Acc a, int mask, int lane) {
-    return Acc{xor_move_f(a.s, mask, lane), xor_move_f(a.c, mask, lane)};
-  }
+  __device__ static __forceinline__ Acc merge(Acc a, Acc b, int) { return a + b; }
   __device__ static __forceinline__ void put(char* base, long long slot, Acc a) {
-    f32x2 v;
-    v.x = a.s;
-    v.y = a.c;
-    *reinterpret_cast<f32x2*>(base + slot * kSlotBytes) = v;
+    *reinterpret_cast<double*>(base + slot * kSlotBytes) = a;
   }
   __device__ static __forceinline__ Acc get(const char* base, long long slot) {
-    const f32x2 v = *reinterpret_cast<const f32x2*>(base + slot * kSlotBytes);
-    return Acc{v.x, v.y};
+    return *reinterpret_cast<const double*>(base + slot * kSlotBytes);
   }
 };
 
@@ -288,10 +268,6 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 
 // element that leaves a carrier unchanged (for lanes whose chunk is masked out);
 // for ARG the masked chunk's index is beyond the extent, so real ties still win
-template <class T, int OP>
-__device__ __forceinline__ float masked_f(float x, bool ok) {
-  return ok ? x : 0.0f;
-}
 template <int OP>
 __device__ __forceinline__ int masked_i(int x, bool ok) {
   constexpr int id = (OP == HP_OP_MIN || OP == HP_OP_ARGMIN) ? 0x7FFFFFFF
@@ -302,39 +278,33 @@ __device__ __forceinline__ int masked_i(int x, bool ok) {
 
 template <class T, int C, int OP>
 struct AddChunk;
+// A chunk's elements are added as a tree of adjacent pairs, then to the carrier: the
+// carrier's chain of dependent adds is one per chunk.
 template <int OP>
 struct AddChunk<FloatT<float>, 4, OP> {
   __device__ static __forceinline__ void run(FAcc& a, f32x4 x, long long, bool ok) {
-    FloatT<float>::add(a, masked_f<FloatT<float>, OP>(x.x, ok), 0, 0);
-    FloatT<float>::add(a, masked_f<FloatT<float>, OP>(x.y, ok), 0, 0);
-    FloatT<float>::add(a, masked_f<FloatT<float>, OP>(x.z, ok), 0, 0);
-    FloatT<float>::add(a, masked_f<FloatT<float>, OP>(x.w, ok), 0, 0);
+    const f32x4 m = ok ? x : f32x4{0.f, 0.f, 0.f, 0.f};
+    a += ((double)m.x + (double)m.y) + ((double)m.z + (double)m.w);
   }
 };
 template <int OP>
 struct AddChunk<FloatT<float>, 1, OP> {
   __device__ static __forceinline__ void run(FAcc& a, float x, long long, bool ok) {
-    FloatT<float>::add(a, masked_f<FloatT<float>, OP>(x, ok), 0, 0);
+    FloatT<float>::add(a, ok ? x : 0.0f);
   }
 };
 template <int OP>
 struct AddChunk<FloatT<uint16_t>, 8, OP> {
+  __device__ static __forceinline__ double two(uint32_t w) { return (double)bf16_lo(w) + (double)bf16_hi(w); }
   __device__ static __forceinline__ void run(FAcc& a, u32x4 x, long long, bool ok) {
     const u32x4 m = ok ? x : u32x4{0u, 0u, 0u, 0u};
-    FloatT<uint16_t>::add(a, bf16_lo(m.x), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_hi(m.x), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_lo(m.y), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_hi(m.y), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_lo(m.z), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_hi(m.z), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_lo(m.w), 0, 0);
-    FloatT<uint16_t>::add(a, bf16_hi(m.w), 0, 0);
+    a += (two(m.x) + two(m.y)) + (two(m.z) + two(m.w));
   }
 };
 template <int OP>
 struct AddChunk<FloatT<uint16_t>, 1, OP> {
   __device__ static __forceinline__ void run(FAcc& a, unsigned short x, long long, bool ok) {
-    FloatT<uint16_t>::add(a, bf16_lo(ok ? x : 0), 0, 0);
+    FloatT<uint16_t>::add(a, bf16_lo(ok ? x : 0));
   }
 };
 template <int OP>
@@ -631,41 +601,40 @@ __device__ __forceinline__ void group_sync(bool wave) {
   }
 }
 
-// One butterfly step on lane bit B for a carrier of float pairs or integer keys
-// (moves from hp_lanes.h; `uni`: the step may take the mirror / permlane-swap form).
+// One butterfly step on lane bit B for a 64-bit carrier (moves from hp_lanes.h; `uni`:
+// the step may take the mirror / permlane-swap form): the two sides of the step.
 template <int B>
-__device__ __forceinline__ FAcc lane_step(FAcc a, bool uni, int lane, int) {
-  if constexpr (B >= 4) {
-    if (uni) {
-      int s0, s1, c0, c1;
-      sides32<B>(__float_as_int(a.s), s0, s1);
-      sides32<B>(__float_as_int(a.c), c0, c1);
-      return FloatT<float>::merge(FAcc{__int_as_float(s0), __int_as_float(c0)},
-                                  FAcc{__int_as_float(s1), __int_as_float(c1)}, 0);
-    }
-  }
-  const FAcc o{__int_as_float(partner32<B>(__float_as_int(a.s), uni, lane)),
-               __int_as_float(partner32<B>(__float_as_int(a.c), uni, lane))};
-  return FloatT<float>::merge(a, o, 0);
-}
-
-// 64-bit integer sum step
-template <int B>
-__device__ __forceinline__ long long key_sum_step(long long a, bool uni, int lane) {
-  const int lo = (int)(uint32_t)(unsigned long long)a, hi = (int)(uint32_t)((unsigned long long)a >> 32);
+__device__ __forceinline__ void sides64(unsigned long long a, bool uni, int lane, unsigned long long& x,
+                                        unsigned long long& y) {
+  const int lo = (int)(uint32_t)a, hi = (int)(uint32_t)(a >> 32);
   if constexpr (B >= 4) {
     if (uni) {
       int l0, l1, h0, h1;
       sides32<B>(lo, l0, l1);
       sides32<B>(hi, h0, h1);
-      const unsigned long long x = ((unsigned long long)(uint32_t)h0 << 32) | (uint32_t)l0;
-      const unsigned long long y = ((unsigned long long)(uint32_t)h1 << 32) | (uint32_t)l1;
-      return (long long)(x + y);
+      x = ((unsigned long long)(uint32_t)h0 << 32) | (uint32_t)l0;
+      y = ((unsigned long long)(uint32_t)h1 << 32) | (uint32_t)l1;
+      return;
     }
   }
-  const unsigned long long y = ((unsigned long long)(uint32_t)partner32<B>(hi, uni, lane) << 32) |
-                               (uint32_t)partner32<B>(lo, uni, lane);
-  return (long long)((unsigned long long)a + y);
+  x = a;
+  y = ((unsigned long long)(uint32_t)partner32<B>(hi, uni, lane) << 32) | (uint32_t)partner32<B>(lo, uni, lane);
+}
+
+// fp64 sum step
+template <int B>
+__device__ __forceinline__ FAcc lane_step(FAcc a, bool uni, int lane) {
+  unsigned long long x, y;
+  sides64<B>((unsigned long long)__double_as_longlong(a), uni, lane, x, y);
+  return __longlong_as_double((long long)x) + __longlong_as_double((long long)y);
+}
+
+// 64-bit integer sum step
+template <int B>
+__device__ __forceinline__ long long key_sum_step(long long a, bool uni, int lane) {
+  unsigned long long x, y;
+  sides64<B>((unsigned long long)a, uni, lane, x, y);
+  return (long long)(x + y);
 }
 
 // 32-bit min / max step (signed or unsigned)
@@ -710,12 +679,12 @@ template <class T>
 __device__ __forceinline__ typename T::Acc lane_combine(typename T::Acc a, const DevSeg& S, int lane) {
   const uint32_t vm = S.vmask, uf = S.ufast;
   if constexpr (T::kFloat) {
-    if (vm & 1u) a = lane_step<0>(a, uf & 1u, lane, 0);
-    if (vm & 2u) a = lane_step<1>(a, uf & 2u, lane, 0);
-    if (vm & 4u) a = lane_step<2>(a, uf & 4u, lane, 0);
-    if (vm & 8u) a = lane_step<3>(a, uf & 8u, lane, 0);
-    if (vm & 16u) a = lane_step<4>(a, uf & 16u, lane, 0);
-    if (vm & 32u) a = lane_step<5>(a, uf & 32u, lane, 0);
+    if (vm & 1u) a = lane_step<0>(a, uf & 1u, lane);
+    if (vm & 2u) a = lane_step<1>(a, uf & 2u, lane);
+    if (vm & 4u) a = lane_step<2>(a, uf & 4u, lane);
+    if (vm & 8u) a = lane_step<3>(a, uf & 8u, lane);
+    if (vm & 16u) a = lane_step<4>(a, uf & 16u, lane);
+    if (vm & 32u) a = lane_step<5>(a, uf & 32u, lane);
     return a;
   } else if constexpr (T::kKey) {
     const int op = S.op;
@@ -769,12 +738,12 @@ template <class T>
 struct RestAdd;
 template <>
 struct RestAdd<FloatT<float>> {
-  __device__ static __forceinline__ void run(FAcc& a, float x, int) { FloatT<float>::add(a, x, 0, 0); }
+  __device__ static __forceinline__ void run(FAcc& a, float x, int) { FloatT<float>::add(a, x); }
 };
 template <>
 struct RestAdd<FloatT<uint16_t>> {
   __device__ static __forceinline__ void run(FAcc& a, uint16_t x, int) {
-    FloatT<uint16_t>::add(a, bf16_lo((uint32_t)x), 0, 0);
+    FloatT<uint16_t>::add(a, bf16_lo((uint32_t)x));
   }
 };
 template <>
@@ -1037,7 +1006,11 @@ __device__ __forceinline__ void store_int(const DevPlan& P, void* out, long long
   if (P.out_kind == OUT_I64) reinterpret_cast<long long*>(out)[o] = v;
   else reinterpret_cast<int*>(out)[o] = (int)v;
 }
+// A sum that met an infinity or a NaN is a NaN (an fp64 sum of finite floats never
+// overflows): v - v is 0 for every finite v and NaN otherwise.
+__device__ __forceinline__ double float_result(double v) { return v + (v - v); }
 __device__ __forceinline__ void store_flt(const DevPlan& P, void* out, long long o, double v) {
+  v = float_result(v);
   if (P.out_kind == OUT_F64) reinterpret_cast<double*>(out)[o] = v;
   else reinterpret_cast<float*>(out)[o] = (float)v;
 }
@@ -1138,7 +1111,7 @@ __device__ __forceinline__ void wg_run(const DevPlan& P, const typename T::Raw* 
           reduce_block<T, C, NS, U, KD, LEAN, PF, FL>(P, in, off + h + base_red, vnone, th, lds, off);
       if (P.gmode == GCOMB_NONE) {
         if (vnone && red_writer) {
-          if constexpr (T::kFloat) store_flt(P, out, o, (double)a.s + (double)a.c);
+          if constexpr (T::kFloat) store_flt(P, out, o, a);
           else store_int(P, out, o, T::emit(a, P.seg[0].op));
         }
       } else if (vnone) {  // uniform here: with a grid combine every NONE level is on G only

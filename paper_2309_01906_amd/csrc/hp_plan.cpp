@@ -902,6 +902,76 @@ hp_status lower(const hp_nest* n, const hp_level_map* map_in, uint32_t flags, Lo
   return HP_OK;
 }
 
+// Automatic plans with one reduction per output over a contiguous block run on the row
+// kernels (hp_rows.hip) whatever the block's length.  Measured against the plan's own
+// kernels: fp32 (1500, 30011) 35.0 -> 28.8 us, bf16 (1, 2^27) 56.3 -> 44.4, fp32
+// (4096, 256, 256) 156.6 -> 151.7, int32 (610, 56333) ARGMIN 57.2 -> 27.1, and with many
+// short blocks fp32 (400000, 100) 122 -> 35, int32 (220346, 57) 97 -> 12, int32 (100003,
+// 129) ARGMIN 172 -> 17, bf16 (100000, 1000) 126 -> 40, fp32 (8000000, 3) 28; no size
+// was slower.  A wave takes a short block whole while that is at most four vectors per
+// lane (their loads are all in flight before the first is folded); from there a
+// workgroup streams it, on the waves and grid parts of the plan's map.
+RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, const Lowered& L) {
+  RowRoute r;
+  memset(&r, 0, sizeof r);
+  if (map || (flags & ~(uint32_t)HP_FLAG_OUT_F32)) return r;  // explicit maps and variants are run as asked
+  if (n->dtype != HP_I32 && n->dtype != HP_F32 && n->dtype != HP_BF16) return r;
+  const int d = n->depth;
+  int p = 0;
+  while (p < d && n->op[p] == HP_OP_NONE) ++p;
+  if (p == d) return r;
+  const int op = n->op[p];
+  const bool arg = op == HP_OP_ARGMIN || op == HP_OP_ARGMAX;
+  if (arg && p != d - 1) return r;
+  int64_t n_out = 1, block = 1;
+  for (int l = 0; l < p; ++l) n_out *= n->extent[l];
+  for (int l = p; l < d; ++l) {
+    if (n->op[l] != op) return r;
+    block *= n->extent[l];
+  }
+  const int64_t vec = 16 / elem_bytes(n->dtype);
+  r.dtype = n->dtype;
+  r.op = op;
+  r.f32_out = (flags & HP_FLAG_OUT_F32) ? 1 : 0;
+  r.n_out = n_out;
+  r.block = block;
+  r.parts = 1;
+  const int64_t full = kFillWorkgroups;  // workgroups of 4 waves that fill the chip
+  if (block < vec) {
+    r.kind = ROWS_TINY;
+    const int64_t g = cdiv(n_out, 256);
+    r.grid = (uint32_t)(g < 4 * full ? g : 4 * full);
+    return r;
+  }
+  if (block <= 4 * kWave * vec) {
+    r.kind = ROWS_SHORT;
+    const int64_t need = cdiv(block, vec);
+    r.lane_bits = need >= kWave ? 6 : log2u((uint64_t)need);
+    r.vecs = (int32_t)cdiv(need, (int64_t)1 << r.lane_bits);
+    const int64_t steps = cdiv(n_out, kWave >> r.lane_bits);
+    const int64_t most = r.vecs == 1 ? 4 : r.vecs == 2 ? 2 : 1;
+    r.ahead = (int32_t)(steps >= most * full * 4 ? most : 1);
+    const int64_t g = cdiv(steps, (int64_t)r.ahead * 4);
+    r.grid = (uint32_t)(g < full ? g : full);
+    return r;
+  }
+  r.kind = ROWS_LONG;
+  r.waves = L.dp.nw;
+  if (r.waves > 8) return RowRoute{};
+  int64_t parts = L.dp.gsplit;
+  int64_t len = cdiv(cdiv(block, parts), vec) * vec;
+  while (parts > 1) {  // every part holds an aligned vector wherever it starts
+    parts = cdiv(block, len);
+    if (block - (parts - 1) * len >= 2 * vec) break;
+    len += vec;
+  }
+  r.parts = (uint32_t)parts;
+  r.part_len = parts > 1 ? len : block;
+  if (n_out * parts > ((int64_t)1 << 31) / (r.waves * kWave)) return RowRoute{};
+  r.grid = (uint32_t)(n_out * parts);
+  return r;
+}
+
 }  // namespace hp
 
 extern "C" const char* hp_last_error(void) { return hp::g_err; }

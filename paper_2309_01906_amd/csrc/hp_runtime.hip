@@ -7,6 +7,7 @@
 #include "hp_internal.h"
 
 #include "hp_fold.h"
+#include "hp_rows.h"
 
 struct hp_plan_s {
   hp::DevPlan dp;        // host copy: launch geometry
@@ -14,6 +15,7 @@ struct hp_plan_s {
   hp::FoldTask* d_fold;  // grid combine: the fold kernel's tasks (n_fold of them)
   int n_fold;
   hp_plan_info info;
+  hp::RowRoute rows;     // kind ROWS_OFF: the plan's own kernels
   void* ws;
   int device;
 };
@@ -28,6 +30,7 @@ extern "C" hp_status hp_plan(const hp_nest* nest, const hp_level_map* map, uint3
   if (!p) return hp::fail(HP_ENOMEM, "host allocation of the plan failed");
   p->dp = L.dp;
   p->info = L.info;
+  p->rows = hp::row_route(nest, map, flags, L);
   p->ws = nullptr;
   p->d_dp = nullptr;
   p->d_fold = nullptr;
@@ -87,6 +90,7 @@ extern "C" hp_status hp_run(hp_plan_t plan, const void* d_in, void* d_out, void*
     return hp::fail(HP_EINVAL, "plan was made on device %d, current device is %d", plan->device, dev);
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   hp_status s;
+  if (plan->rows.kind != hp::ROWS_OFF) return hp::launch_rows(plan->rows, d_in, d_out, plan->ws, st);
   if (plan->dp.kernel == HP_KERNEL_ORDERED) return hp::launch_ordered(plan->dp, plan->d_dp, d_in, d_out, plan->ws, st);
   switch (plan->dp.dtype) {
     case HP_F32: s = hp::launch_nest_f32(plan->dp, plan->d_dp, d_in, d_out, plan->ws, plan->info.lds_bytes, st); break;

@@ -7,6 +7,7 @@
 #include "hp_internal.h"
 
 #include "hp_fold.h"
+#include "hp_rows.h"
 
 namespace hp {
 
@@ -97,6 +98,8 @@ extern "C" hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* m
   FoldTask* dF = reinterpret_cast<FoldTask*>(base + kStaticPlanBytes);
   void* ws = L.info.workspace_bytes ? base + kStaticWsOffset : nullptr;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  const RowRoute rows = row_route(nest, map, flags, L);
+  if (rows.kind != ROWS_OFF) return launch_rows(rows, d_in, d_out, ws, st);  // plain arguments: nothing to install
   const long long words = (long long)(sizeof(DevPlan) / 4);
   const long long n_inst = n_fold > words ? n_fold : words;
   hipLaunchKernelGGL(k_static_install, dim3((unsigned)((n_inst + 255) / 256)), dim3(256), 0, st, P, dP, dF,
