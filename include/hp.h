@@ -162,8 +162,10 @@ typedef struct hp_plan_info {
  * mapping; they differ in which code paths are compiled in.  An automatic plan (no
  * map, no flag but HP_FLAG_OUT_F32) with one reduction per output over a contiguous
  * block -- float sums of sums, int32 with one operator or one ARG level -- is run by
- * the row kernels instead (csrc/hp_rows.hip): the same outputs, waves and grid parts,
- * without a plan in memory; `kernel` then names the variant that the map would take. */
+ * the row kernels instead (csrc/hp_rows.hip), and one of two or three int32 segments by
+ * the segment kernels (csrc/hp_segs.hip): the same outputs without a plan in memory;
+ * `kernel` and the geometry then describe the map that the plan's own kernels would
+ * take, and the workspace may be larger than workspace_bytes. */
 typedef enum hp_kernel {
   HP_KERNEL_LEAN = 0,     /* float, depth <= 4, at most one strided inner dim, <= 8 waves, vector chunk */
   HP_KERNEL_GENERIC4 = 1, /* float, depth <= 4 */

@@ -138,6 +138,31 @@ struct RowRoute {
   int64_t part_len;   // long: elements per workgroup (the last may have fewer)
 };
 
+// How hp_run launches an automatic int32 plan of two or three reducing segments
+// (hp_segs.hip): out[o] = Q over q < eQ of M over m < eM of L over rows of eL elements.
+enum SegKind : int32_t { SEGS_OFF = 0, SEGS_SHORT, SEGS_LONG };
+struct SegRoute {
+  int32_t kind;
+  int32_t opQ, opM, opL;
+  int32_t eQ, eM, eL;
+  int32_t out64;      // int64 outputs
+  int64_t n_out;
+  int32_t lane_bits;  // short: 2^lane_bits lanes per row
+  int32_t vecs;       // short: vectors per lane (-1 to -3: rows of that many elements, a lane each)
+  int32_t waves;      // short: waves per (o, q) pair and part (1: runs of pairs)
+  int32_t pair_bits;  // short, runs: 2^pair_bits pairs side by side in a wave
+  int32_t run;        // short, runs: pairs (or groups of 2^pair_bits) per wave
+  uint32_t grid;      // short, runs: workgroups of four waves
+  int32_t steps;      // short: steps of 64 / 2^lane_bits rows in M
+  int32_t per;        // short: steps per part
+  uint32_t parts;     // short: workgroups per pair
+  uint32_t units;     // short: pairs * parts
+  int32_t tail;       // short: the pairs' carriers go to ws and the tail kernel ends the nest
+  RowRoute rows;      // long: the pass that reduces every row to a value
+  uint64_t parts_off; // long: where that pass keeps the partials of split rows in ws
+  uint64_t ws_bytes;
+};
+
 // Host-side result of planning (no device resources).
 struct Lowered {
   DevPlan dp;
@@ -146,6 +171,8 @@ struct Lowered {
 
 // The row route of a nest that `lower` planned into L (kind ROWS_OFF: none).
 RowRoute row_route(const hp_nest* nest, const hp_level_map* map, uint32_t flags, const Lowered& L);
+// The segment route of one (kind SEGS_OFF: none).
+SegRoute seg_route(const hp_nest* nest, const hp_level_map* map, uint32_t flags, const Lowered& L);
 
 // Fill `out` from nest + map; sets the thread-local error text on failure.
 // force_nw > 0 (batched plans): the plan must use exactly that many waves per

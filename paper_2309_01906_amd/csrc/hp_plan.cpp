@@ -972,6 +972,113 @@ RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   return r;
 }
 
+// Automatic int32 plans of two or three segments run on the segment kernels (hp_segs.hip),
+// which read rows of any length as vectors where the plan's kernels fall back to single
+// elements, walk no odometer and split rows as well as M over the chip.  Measured against
+// the plan's kernels: (61, 125, 67, 59) SUM, MAX, ARGMIN 105 -> 31 us, (1024, 64, 1024)
+// ARGMAX of SUM 75 -> 42, the chain (64, 128, 64, 64) 34.6 -> 31.5, (4096, 16, 1024) SUM
+// of MAX 44.3 -> 41.8, (16777, 2048, 2) MAX of SUM 530 -> 52, (1, 2, 2^24) SUM of MAX
+// 8,306 -> 25, (1000000, 3, 5) MAX of SUM 849 -> 36; none was slower.
+//   Rows of up to four vectors per lane go with M in one pass; longer ones through the
+// row kernels first (their values are at most 1/512 of the input).
+//   Waves per pair: 4,096 waves in all where that takes more than one per pair
+// ((1024, 64, 1024): 4 waves a pair 42 us, 8 waves 49 us), at least two steps each.
+SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, const Lowered& L) {
+  SegRoute S, off;
+  memset(&S, 0, sizeof S);
+  memset(&off, 0, sizeof off);
+  if (map || (flags & ~(uint32_t)HP_FLAG_OUT_F32) || n->dtype != HP_I32) return off;
+  const int d = n->depth;
+  int p = 0;
+  while (p < d && n->op[p] == HP_OP_NONE) ++p;
+  int64_t n_out = 1;
+  for (int l = 0; l < p; ++l) n_out *= n->extent[l];
+  // segments, outermost first; a SUM / MIN / MAX level of one iteration passes its value on
+  int op[3], ns = 0;
+  int64_t e[3];
+  for (int l = p; l < d; ++l) {
+    const bool arg = n->op[l] == HP_OP_ARGMIN || n->op[l] == HP_OP_ARGMAX;
+    if (!arg && n->extent[l] == 1) continue;
+    if (!arg && ns && op[ns - 1] == n->op[l]) {
+      e[ns - 1] *= n->extent[l];
+      continue;
+    }
+    if (ns == 3) return off;
+    op[ns] = n->op[l];
+    e[ns++] = n->extent[l];
+  }
+  if (ns < 2 || (ns == 3 && e[0] == 1)) return off;  // (an ARG level of one iteration outside: always 0)
+  const int64_t lim = (int64_t)1 << 30;
+  if (e[ns - 1] >= lim || e[ns - 2] >= lim || (ns == 3 && e[0] >= lim)) return off;
+  S.opL = op[ns - 1];
+  S.opM = op[ns - 2];
+  S.opQ = ns == 3 ? op[0] : HP_OP_NONE;
+  S.eL = (int32_t)e[ns - 1];
+  S.eM = (int32_t)e[ns - 2];
+  S.eQ = ns == 3 ? (int32_t)e[0] : 1;
+  S.out64 = L.dp.out_kind == OUT_I64 ? 1 : 0;
+  S.n_out = n_out;
+  const int64_t want = kFillWorkgroups * 4;  // waves that fill the chip
+  const int64_t pairs = n_out * S.eQ;
+  if (pairs > lim / S.eM) return off;
+  if (S.eL > 4 * kWave * 4) {
+    const int64_t rows = pairs * S.eM;
+    RowRoute& r = S.rows;
+    r.kind = ROWS_LONG;
+    r.dtype = HP_I32;
+    r.op = S.opL;
+    r.n_out = rows;
+    r.block = S.eL;
+    int64_t nw = cdiv(want, rows);                   // waves per row that fill the chip
+    const int64_t most = cdiv(S.eL, 4 * kWave * 4);  // each with at least 4 vectors per lane
+    if (nw > most) nw = most;
+    r.waves = nw > 4 ? 8 : nw > 2 ? 4 : nw > 1 ? 2 : 1;
+    int64_t parts = nw / 8 < 1 ? 1 : nw / 8;
+    int64_t len = cdiv(cdiv(S.eL, parts), 4) * 4;
+    while (parts > 1) {
+      parts = cdiv(S.eL, len);
+      if (S.eL - (parts - 1) * len >= 8) break;
+      len += 4;
+    }
+    r.parts = (uint32_t)parts;
+    r.part_len = parts > 1 ? len : S.eL;
+    if (rows * parts > ((int64_t)1 << 31) / (r.waves * kWave)) return off;
+    r.grid = (uint32_t)(rows * parts);
+    S.kind = SEGS_LONG;
+    S.parts_off = (uint64_t)cdiv(rows * 8, 256) * 256;
+    S.ws_bytes = S.parts_off + (parts > 1 ? (uint64_t)rows * parts * 8 : 0);
+    return S;
+  }
+  if ((int64_t)S.eM * S.eL > ((int64_t)1 << 28)) return off;  // 32-bit byte offsets inside a pair
+  const int64_t need = cdiv(S.eL, 4);
+  S.lane_bits = S.eL < 4 ? 0 : need >= kWave ? 6 : log2u((uint64_t)need);
+  S.vecs = S.eL < 4 ? -S.eL : (int32_t)cdiv(need, (int64_t)1 << S.lane_bits);
+  const int64_t rows = kWave >> S.lane_bits;
+  while (2 * (int64_t)S.eM <= (rows >> S.pair_bits)) ++S.pair_bits;
+  const int64_t steps = cdiv(S.eM, rows >> S.pair_bits);
+  S.steps = (int32_t)steps;
+  int64_t nw = cdiv(want / 2, pairs);  // waves per pair that fill the chip, each with two steps or more
+  if (nw > steps / 2) nw = steps / 2;
+  S.waves = nw > 4 ? 8 : nw > 1 ? 4 : 1;
+  int64_t parts = nw / 8 < 1 ? 1 : nw / 8;
+  const int64_t per = cdiv(steps, parts);
+  parts = cdiv(steps, per);
+  S.per = (int32_t)per;
+  S.parts = (uint32_t)parts;
+  if (pairs * parts > ((int64_t)1 << 31) / (8 * kWave)) return off;
+  S.units = (uint32_t)(pairs * parts);
+  if (S.waves == 1) {
+    const int64_t groups = cdiv(pairs, (int64_t)1 << S.pair_bits);
+    S.run = (int32_t)cdiv(groups, want);
+    S.grid = (uint32_t)cdiv(cdiv(groups, S.run), 4);
+  }
+  S.tail = (S.eQ > 1 || parts > 1) ? 1 : 0;
+  if (S.tail && parts == 1 && (int64_t)S.eM * S.eL < 8) return off;  // the carriers would outweigh the input
+  S.ws_bytes = S.tail ? (uint64_t)S.units * kSlotBytes : 0;
+  S.kind = SEGS_SHORT;
+  return S;
+}
+
 }  // namespace hp
 
 extern "C" const char* hp_last_error(void) { return hp::g_err; }

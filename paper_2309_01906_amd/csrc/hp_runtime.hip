@@ -8,6 +8,7 @@
 
 #include "hp_fold.h"
 #include "hp_rows.h"
+#include "hp_segs.h"
 
 struct hp_plan_s {
   hp::DevPlan dp;        // host copy: launch geometry
@@ -15,7 +16,8 @@ struct hp_plan_s {
   hp::FoldTask* d_fold;  // grid combine: the fold kernel's tasks (n_fold of them)
   int n_fold;
   hp_plan_info info;
-  hp::RowRoute rows;     // kind ROWS_OFF: the plan's own kernels
+  hp::RowRoute rows;     // kind ROWS_OFF and SEGS_OFF: the plan's own kernels
+  hp::SegRoute segs;
   void* ws;
   int device;
 };
@@ -31,6 +33,7 @@ extern "C" hp_status hp_plan(const hp_nest* nest, const hp_level_map* map, uint3
   p->dp = L.dp;
   p->info = L.info;
   p->rows = hp::row_route(nest, map, flags, L);
+  p->segs = hp::seg_route(nest, map, flags, L);
   p->ws = nullptr;
   p->d_dp = nullptr;
   p->d_fold = nullptr;
@@ -54,14 +57,25 @@ extern "C" hp_status hp_plan(const hp_nest* nest, const hp_level_map* map, uint3
     delete p;
     return hp::fail(HP_EDEVICE, "device plan upload failed");
   }
-  if (p->info.workspace_bytes) {
-    if (hipMalloc(&p->ws, p->info.workspace_bytes) != hipSuccess) {
+  size_t ws_bytes = p->info.workspace_bytes;
+  if (p->segs.kind != hp::SEGS_OFF && p->segs.ws_bytes > ws_bytes) {
+    // the segment kernels' carriers; where they do not fit, the plan's own kernels run
+    if (hipMalloc(&p->ws, p->segs.ws_bytes) == hipSuccess) {
+      ws_bytes = p->segs.ws_bytes;
+    } else {
+      (void)hipGetLastError();
+      p->ws = nullptr;
+      p->segs.kind = hp::SEGS_OFF;
+    }
+  }
+  if (ws_bytes) {
+    if (!p->ws && hipMalloc(&p->ws, ws_bytes) != hipSuccess) {
       (void)hipFree(p->d_dp);
       delete p;
       return hp::fail(HP_ENOMEM, "workspace allocation of %zu bytes failed", L.info.workspace_bytes);
     }
     // every run writes all partials before the fold reads them; cleared for tidiness
-    if (hipMemset(p->ws, 0, p->info.workspace_bytes) != hipSuccess) {
+    if (hipMemset(p->ws, 0, ws_bytes) != hipSuccess) {
       (void)hipFree(p->ws);
       (void)hipFree(p->d_dp);
       delete p;
@@ -91,6 +105,7 @@ extern "C" hp_status hp_run(hp_plan_t plan, const void* d_in, void* d_out, void*
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   hp_status s;
   if (plan->rows.kind != hp::ROWS_OFF) return hp::launch_rows(plan->rows, d_in, d_out, plan->ws, st);
+  if (plan->segs.kind != hp::SEGS_OFF) return hp::launch_segs(plan->segs, d_in, d_out, plan->ws, st);
   if (plan->dp.kernel == HP_KERNEL_ORDERED) return hp::launch_ordered(plan->dp, plan->d_dp, d_in, d_out, plan->ws, st);
   switch (plan->dp.dtype) {
     case HP_F32: s = hp::launch_nest_f32(plan->dp, plan->d_dp, d_in, d_out, plan->ws, plan->info.lds_bytes, st); break;

@@ -8,6 +8,7 @@
 
 #include "hp_fold.h"
 #include "hp_rows.h"
+#include "hp_segs.h"
 
 namespace hp {
 
@@ -100,6 +101,8 @@ extern "C" hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* m
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const RowRoute rows = row_route(nest, map, flags, L);
   if (rows.kind != ROWS_OFF) return launch_rows(rows, d_in, d_out, ws, st);  // plain arguments: nothing to install
+  const SegRoute segs = seg_route(nest, map, flags, L);
+  if (segs.kind != SEGS_OFF && segs.ws_bytes <= kStaticWsBytes) return launch_segs(segs, d_in, d_out, base + kStaticWsOffset, st);
   const long long words = (long long)(sizeof(DevPlan) / 4);
   const long long n_inst = n_fold > words ? n_fold : words;
   hipLaunchKernelGGL(k_static_install, dim3((unsigned)((n_inst + 255) / 256)), dim3(256), 0, st, P, dP, dF,

@@ -1,0 +1,89 @@
+"""Segment kernels: automatic int32 plans of two or three reducing segments.  Rows and
+middle levels at the edges of every shape the route picks -- rows shorter than a vector,
+one to four vectors per lane, longer rows reduced by the row kernels; several pairs side
+by side in a wave, a run of pairs per wave, waves sharing a pair, parts and the tail --
+against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import paper_2309_01906_amd as hp
+import workloads
+from gpu_util import assert_match, gpu_reduce, say, to_device
+
+pytestmark = pytest.mark.gpu
+
+TWO = [("SUM", "MAX"), ("ARGMAX", "SUM"), ("MIN", "SUM"), ("SUM", "ARGMIN"), ("ARGMIN", "ARGMAX"), ("MAX", "MIN")]
+THREE = [("SUM", "MAX", "ARGMIN"), ("ARGMAX", "SUM", "MIN"), ("MIN", "ARGMIN", "SUM"), ("ARGMIN", "MAX", "ARGMAX")]
+
+
+def check(ext, ops, lo, hi, seed):
+    say("case segs", ext, ops)
+    x = workloads.uniform_i32(seed, ext, lo, hi)
+    got, _ = gpu_reduce(x, ext, ops)
+    assert_match(got, x, ext, ops, what=f"segs {ext} {ops}")
+
+
+@pytest.mark.parametrize("ops", TWO)
+@pytest.mark.parametrize("rows", [1, 2, 3, 4, 5, 7, 16, 33, 63, 64, 65, 255, 256, 257, 500, 513, 769, 1023, 1024, 1025, 4100])
+def test_two_segments(ops, rows):
+    for m, n in [(1, 5), (2, 70), (3, 300), (17, 33), (64, 9), (65, 3), (1000, 1)]:
+        check((n, m, rows), ("NONE",) + ops, -(1 << 31), (1 << 31) - 1, 300 + rows)  # sums beyond 32 bits
+        check((n, m, rows), ("NONE",) + ops, -2, 2, 301 + rows)                       # ties
+
+
+@pytest.mark.parametrize("ops", THREE)
+@pytest.mark.parametrize("rows", [1, 3, 4, 9, 64, 100, 1000, 1030])
+def test_three_segments(ops, rows):
+    for q, m, n in [(2, 2, 40), (3, 7, 5000), (70, 3, 2), (9, 33, 11), (1500, 2, 1), (5, 300, 3)]:
+        if n * q * m * rows < 1 << 23:
+            check((n, q, m, rows), ("NONE",) + ops, -3, 3, 310 + rows)
+
+
+@pytest.mark.parametrize("ext,ops", [
+    ((1, 2, 1 << 21), ("SUM", "MAX")), ((1, 3, 700001), ("ARGMAX", "SUM")),     # rows split over workgroups
+    ((1, 200001, 2), ("MAX", "SUM")), ((2, 50001, 33), ("ARGMIN", "MAX")),      # M split into parts
+    ((9000, 3, 5), ("SUM", "MIN")), ((20011, 9, 40), ("ARGMAX", "SUM")),        # runs of pairs
+    ((6000, 4, 5, 6), ("SUM", "MAX", "SUM")), ((40, 900, 65, 7), ("MIN", "SUM", "ARGMAX"))])
+def test_many_pairs_and_parts(ext, ops):
+    check(ext, ("NONE",) + ops, -1000, 1000, 320)
+
+
+def test_levels_that_merge_and_single_iterations():
+    """Adjacent levels of one operator are one segment, levels of one iteration pass
+    their value on, and an ARG level of one iteration gives 0."""
+    for ext, ops in [((7, 3, 1, 5, 6), ("NONE", "SUM", "MIN", "MAX", "MAX")), ((64, 1, 2, 100), ("NONE", "ARGMAX", "ARGMIN", "MIN")),
+                     ((5, 4, 3, 2, 30), ("NONE", "SUM", "SUM", "MAX", "MAX")), ((8, 9, 1, 40), ("NONE", "MAX", "ARGMIN", "SUM")),
+                     ((6, 50, 1), ("NONE", "MIN", "ARGMAX")), ((4, 6, 5, 1), ("NONE", "ARGMAX", "MIN", "SUM"))]:
+        check(ext, ops, -50, 50, 330)
+
+
+@pytest.mark.parametrize("fill,mm", [(np.iinfo(np.int32).max, "MIN"), (np.iinfo(np.int32).min, "MAX")])
+def test_extreme_rows(fill, mm):
+    for ext in [(5, 7, 3), (5, 40, 67), (2, 9, 2000)]:
+        x = np.full(ext, fill, np.int32)
+        for ops in [("NONE", "ARG" + mm, mm), ("NONE", mm, "ARG" + mm), ("NONE", "SUM", "ARG" + mm), ("NONE", mm, "SUM")]:
+            got, _ = gpu_reduce(x, ext, ops)
+            assert_match(got, x, ext, ops, what=f"extremes {ext} {ops}")
+
+
+def test_static_entry_and_graph_replay():
+    """The allocation-free entry point gives the same bits, and a captured run replays on
+    new values."""
+    import torch
+    for ext, ops in [((9, 40, 33, 21), ("NONE", "SUM", "MAX", "ARGMIN")), ((3, 5, 5000), ("NONE", "ARGMAX", "SUM"))]:
+        x = to_device(workloads.uniform_i32(340, ext, -1000, 1000))
+        with hp.Plan(ext, ops, hp.I32) as p:
+            a, b = p.empty_out("cuda"), p.empty_out("cuda")
+            p.run(x, a)
+            hp.reduce_static(x, b, ext, ops)
+            assert torch.equal(a, b)
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                p.run(x, b)
+            for k in range(3):
+                x.add_(k + 1)
+                x[0] *= -1
+                g.replay()
+                p.run(x, a)
+                torch.cuda.synchronize()
+                assert torch.equal(a, b)
