@@ -13,7 +13,9 @@ counts: ``("GW", {"G": 16, "W": 8})``.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libhp.so")
@@ -103,16 +105,41 @@ def _op(o):
     return OP_NAMES[o.upper()] if isinstance(o, str) else int(o)
 
 
-def make_nest(extents, ops, dtype) -> Nest:
-    n = Nest()
-    if len(extents) != len(ops) or not 1 <= len(extents) <= MAX_DEPTH:
+_NEST = struct.Struct(f"={2 + MAX_DEPTH}i{MAX_DEPTH}q")  # the layout of Nest
+assert _NEST.size == ctypes.sizeof(Nest)
+_PAD = [(0,) * (MAX_DEPTH - d) for d in range(MAX_DEPTH + 1)]
+
+
+@functools.lru_cache(maxsize=1024)
+def _op_codes(ops: tuple) -> tuple:
+    """The op codes of a nest's levels, padded (a stream of requests repeats few chains)."""
+    return tuple(_op(o) for o in ops) + _PAD[len(ops)]
+
+
+def _pack_nest(extents, ops, dtype) -> bytes:
+    """The bytes of a Nest (one pack instead of a ctypes store per field: a batch or a
+    burst of requests marshals thousands)."""
+    d = len(extents)
+    if d != len(ops) or not 1 <= d <= MAX_DEPTH:
         raise ValueError("extents and ops must have the same length, 1..8")
-    n.depth = len(extents)
-    n.dtype = int(dtype)
-    for i, (e, o) in enumerate(zip(extents, ops)):
-        n.extent[i] = int(e)
-        n.op[i] = _op(o)
-    return n
+    try:
+        return _NEST.pack(d, dtype, *_op_codes(tuple(ops)), *extents, *_PAD[d])
+    except (struct.error, TypeError):
+        # not a plain whole number, or one beyond its field: int() and ctypes convert it
+        n = Nest()
+        n.depth, n.dtype = d, int(dtype)
+        for i, (e, o) in enumerate(zip(extents, ops)):
+            n.extent[i], n.op[i] = int(e), _op(o)
+        return bytes(n)
+
+
+def make_nest(extents, ops, dtype) -> Nest:
+    return Nest.from_buffer_copy(_pack_nest(extents, ops, dtype))
+
+
+def _make_nests(nests):
+    """An array of Nest from (extents, ops, dtype) triples."""
+    return (Nest * len(nests)).from_buffer_copy(b"".join([_pack_nest(e, o, d) for e, o, d in nests]))
 
 
 def make_map(level_map) -> LevelMap | None:
@@ -185,9 +212,18 @@ def inspect(extents, ops, dtype, level_map=None, flags: int = 0) -> dict:
     return _info_dict(inf, ops)
 
 
+_torch_module = None
+_raw_stream = _raw_device = None  # torch's current stream handle and device, where it offers them directly
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module, _raw_stream, _raw_device
+    if _torch_module is None:
+        import torch
+        _raw_device = getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if _raw_device is not None else None
+        _torch_module = torch
+    return _torch_module
 
 
 def torch_out_dtype(code):
@@ -208,10 +244,21 @@ def dtype_of(t) -> int:
 
 
 def _stream_handle(stream):
-    torch = _torch()
+    """The hipStream_t of a torch stream (None: the current one) or of an integer."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        torch = _torch()
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())  # 0.2 us where building a torch.cuda.Stream takes 2.9 us
+        return torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _in_dtypes(dtype):
+    """The tensor types a plan of this element type takes."""
+    torch = _torch()
+    if dtype in WIDTH:
+        return (torch.int64,)
+    return {I32: (torch.int32,), F32: (torch.float32,), BF16: (torch.bfloat16, torch.int16, torch.uint16)}[dtype]
 
 
 class Plan:
@@ -219,6 +266,7 @@ class Plan:
 
     def __init__(self, extents, ops, dtype, level_map=None, flags: int = 0):
         self._h = ctypes.c_void_p()
+        self._sig = None
         self.extents = tuple(int(e) for e in extents)
         self.ops = tuple(_op(o) for o in ops)
         self.dtype = int(dtype)
@@ -237,25 +285,29 @@ class Plan:
     def empty_out(self, device):
         return _torch().empty(self._out_shape(), dtype=torch_out_dtype(self.info["out_dtype"]), device=device)
 
+    def _signature(self):
+        """What run() checks its tensors against (needs torch, so made at the first run)."""
+        self._sig = (self.info["in_elems"] * WIDTH.get(self.dtype, 1), _in_dtypes(self.dtype), self._out_shape(),
+                     torch_out_dtype(self.info["out_dtype"]), lib().hp_run)
+        return self._sig
+
     def run(self, inp, out=None, stream=None):
-        torch = _torch()
+        in_numel, in_dtypes, out_shape, out_dtype, hp_run = self._sig or self._signature()
         if not inp.is_cuda:
             raise ValueError("input must be a device tensor")
         if not inp.is_contiguous():
             raise ValueError("input must be contiguous")
-        w = WIDTH.get(self.dtype)
-        if w is not None:  # ordered-product elements: int64 words, w per element
-            if inp.dtype != torch.int64 or inp.numel() != self.info["in_elems"] * w:
-                raise ValueError("input does not match the planned nest")
-        elif inp.numel() != self.info["in_elems"] or dtype_of(inp) != self.dtype:
+        if inp.numel() != in_numel or inp.dtype not in in_dtypes:
+            if inp.numel() == in_numel and self.dtype not in WIDTH:
+                dtype_of(inp)  # a TypeError for a type no nest takes
             raise ValueError("input does not match the planned nest")
         if out is None:
             out = self.empty_out(inp.device)
-        if tuple(out.shape) != self._out_shape() or out.dtype != torch_out_dtype(self.info["out_dtype"]) \
-                or not out.is_contiguous():
+        if out.shape != out_shape or out.dtype != out_dtype or not out.is_contiguous():
             raise ValueError("output does not match the plan")
-        check(lib().hp_run(self._h, ctypes.c_void_p(inp.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                           _stream_handle(stream)))
+        status = hp_run(self._h, inp.data_ptr(), out.data_ptr(), _stream_handle(stream))
+        if status:
+            check(status)
         return out
 
     __call__ = run
@@ -312,8 +364,7 @@ class Stencil:
             out = torch.empty_like(inp)
         if out.dtype != torch.float32 or tuple(out.shape) != self.shape or not out.is_contiguous():
             raise ValueError("output does not match the plan")
-        check(lib().hp_stencil_run(self._h, ctypes.c_void_p(inp.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                                   _stream_handle(stream)))
+        check(lib().hp_stencil_run(self._h, inp.data_ptr(), out.data_ptr(), _stream_handle(stream)))
         return out
 
     def close(self):
@@ -390,8 +441,7 @@ def reduce_static(inp, out, extents, ops, level_map=None, flags: int = 0, stream
     if not (inp.is_cuda and out.is_cuda and inp.is_contiguous() and out.is_contiguous()):
         raise ValueError("input and output must be contiguous device tensors")
     check(lib().hp_reduce_static(ctypes.byref(n), ctypes.byref(m) if m is not None else None, flags,
-                                 ctypes.c_void_p(inp.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                                 _stream_handle(stream)))
+                                 inp.data_ptr(), out.data_ptr(), _stream_handle(stream)))
     return out
 
 
@@ -434,9 +484,7 @@ def _batch_sigs():
 def batch_inspect(nests, flags: int = 0):
     """Host only: the plan of every nest of a batch (tuner cache included)."""
     _batch_sigs()
-    arr = (Nest * len(nests))()
-    for i, (ext, ops, dt) in enumerate(nests):
-        arr[i] = make_nest(ext, ops, dt)
+    arr = _make_nests(nests)
     infos = (PlanInfo * len(nests))()
     check(lib().hp_batch_plan_inspect(arr, len(nests), flags, infos))
     return [_info_dict(infos[i], nests[i][1]) for i in range(len(nests))]
@@ -447,9 +495,7 @@ class Batch:
 
     def __init__(self, nests, flags: int = 0):
         _batch_sigs()
-        arr = (Nest * len(nests))()
-        for i, (ext, ops, dt) in enumerate(nests):
-            arr[i] = make_nest(ext, ops, dt)
+        arr = _make_nests(nests)
         self._h = ctypes.c_void_p()
         self.n = len(nests)
         self._ops = [ops for _, ops, _ in nests]
@@ -581,8 +627,13 @@ def _server_sigs():
     _server_sigs_done = True
 
 
+_REQ_KEYS = tuple(k for k, _ in ReqInfo._fields_ if k != "pad")
+_REQ = struct.Struct("=i4x4d2q")
+assert _REQ.size == ctypes.sizeof(ReqInfo)
+
+
 def _info(ri: ReqInfo) -> dict:
-    return {k: getattr(ri, k) for k, _ in ReqInfo._fields_ if k != "pad"}
+    return dict(zip(_REQ_KEYS, _REQ.unpack_from(ri)))
 
 
 class Server:
@@ -647,9 +698,7 @@ class Server:
 
     def _replay(self, nests, in_ptrs, out_ptrs, times):
         n = len(nests)
-        arr = (Nest * n)()
-        for i, (ext, ops, dt) in enumerate(nests):
-            arr[i] = make_nest(ext, ops, dt)
+        arr = _make_nests(nests)
         ins = (ctypes.c_void_p * n)(*in_ptrs)
         outs = (ctypes.c_void_p * n)(*out_ptrs)
         tk = (ctypes.c_uint64 * n)()
