@@ -403,11 +403,11 @@ def stencils(stream, steps=20, warmup=3):
 
 
 def batched_vs_plain(stream, steps=20, warmup=3, plain=True, verify=True):
-    """10,000 uneven bf16 nests: one persistent launch replayed from a hipGraph vs one
+    """10,000 uneven bf16 nests: one launch replayed from a hipGraph vs one
     launch per nest (eager, and all launches captured in one graph).  Same plans, so
     the outputs are compared bit for bit.  Latency: each run timed alone (p50/p99).
     Throughput: `back_to_back_*`, 50 runs enqueued back to back between two events;
-    the same persistent launches also without the graph (`batched_direct`)."""
+    the same launches also without the graph (`batched_direct`)."""
     import numpy as np
     import torch
 
@@ -613,7 +613,7 @@ def main():
     ap.add_argument("--copy-calib", action="store_true",
                     help="also run one 1 GiB device copy (for scaling rocprofv3 byte counters)")
     ap.add_argument("--batched-only", action="store_true",
-                    help="only the persistent batched run of the 10,000-nest workload (for profiling)")
+                    help="only the batched run of the 10,000-nest workload (for profiling)")
     ap.add_argument("--ordered-only", action="store_true",
                     help="only the ordered products (for profiling the ordered kernels)")
     ap.add_argument("--stencil-only", action="store_true",

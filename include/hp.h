@@ -237,16 +237,24 @@ hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* map, uint32_
                            void* d_out, void* stream);
 
 /* ---------------------------------------------------------------------------
- * Batches: many nests of uneven sizes in one persistent launch per kernel family.
- * Nests are planned as one-wavefront plans, and every wavefront of the persistent
- * workgroups is an independent worker: it starts on tasks dealt to it statically
- * and then takes (nest, workgroup) tasks from an atomic counter -- a dynamic
- * schedule on the grid level (section 3.5).  Tasks go largest first, each to the
- * least-loaded of 64 queues, 8 per XCD.  Grid-split nests are folded by a second
- * kernel after the persistent one, which also resets the task counters for the
- * next run.  Every nest keeps the plan it would get alone (its own shape and the
- * tuner cache decide it, never the batch), so its result is the same bits as a
- * single run of that plan.  Ordered products (HP_OP_PROD) are not batched.
+ * Batches: many nests of uneven sizes in one launch per kernel family.  Nests are
+ * planned as one-wavefront plans.
+ *
+ * A nest of one to three reducing segments (adjacent levels of one operator are one
+ * segment) runs as unit tasks: one-wavefront pieces of some tens of KiB of its input,
+ * one launch per element type, the largest pieces first.  Nests cut into pieces, and
+ * those of three segments, are folded by a second kernel.
+ *
+ * Other nests run as tasks of their plans: every wavefront of persistent workgroups is
+ * an independent worker that starts on tasks dealt to it statically and then takes
+ * (nest, workgroup) tasks from an atomic counter -- a dynamic schedule on the grid level
+ * (section 3.5).  Tasks go largest first, each to the least-loaded of 64 queues, 8 per
+ * XCD.  Grid-split nests are folded by a second kernel after the persistent one, which
+ * also resets the task counters for the next run.
+ *
+ * A nest's own shape and the tuner cache decide its pieces, never the batch, so its
+ * result is the same bits as a launch of its own (hp_batch_run_each).  Ordered products
+ * (HP_OP_PROD) are not batched.
  */
 typedef struct hp_batch_s* hp_batch_t;
 
@@ -267,8 +275,8 @@ hp_status hp_batch_plan_inspect(const hp_nest* nests, int64_t n, uint32_t flags,
 /* Planner decisions for nest i of the batch. */
 hp_status hp_batch_info(hp_batch_t b, int64_t i, hp_plan_info* info);
 
-/* Launch count (persistent kernels per run), total tasks, wavefront workers of the
- * persistent launches, and the algorithmic bytes (inputs + outputs) of one run.
+/* Launch count (kernels per run without the folds), total tasks, wavefronts of those
+ * launches, and the algorithmic bytes (inputs + outputs) of one run.
  * Any output pointer may be NULL. */
 hp_status hp_batch_stats(hp_batch_t b, int64_t* n_launches, int64_t* n_tasks, int64_t* n_workers, double* bytes);
 
@@ -277,7 +285,7 @@ hp_status hp_batch_stats(hp_batch_t b, int64_t* n_launches, int64_t* n_tasks, in
  * table (synchronous); a captured graph stays valid across calls. */
 hp_status hp_batch_set_io(hp_batch_t b, const void* const* d_in, void* const* d_out);
 
-/* Run all nests: one persistent launch per kernel family (or one graph launch
+/* Run all nests: one launch per kernel family (or one graph launch
  * with HP_BATCH_GRAPH, captured at the first call).  Asynchronous on `stream`;
  * must not overlap another run of the same batch.  HP_ESTATE before set_io. */
 hp_status hp_batch_run(hp_batch_t b, void* stream);
@@ -295,7 +303,7 @@ hp_status hp_batch_destroy(hp_batch_t b);
  * candidate level maps of its size class on the current device -- the block seen
  * as (J, K) rows split between grid, waves and lane partitions, or many outputs
  * per task on lane partitions -- and store the fastest in the process-wide cache
- * that batched plans consult.  A candidate is timed as a persistent batch of
+ * that batched plans consult.  A candidate is timed as a batch of
  * replicas of the nest (its throughput when it shares the device), median of
  * `reps` runs, per nest.  best_us / auto_us (may be NULL) receive the winner's
  * time and the automatic map's.  The cache is also read once from the file named

@@ -491,7 +491,7 @@ def batch_inspect(nests, flags: int = 0):
 
 
 class Batch:
-    """hp_batch_*: many nests, one persistent launch per kernel family."""
+    """hp_batch_*: many nests, one launch per kernel family."""
 
     def __init__(self, nests, flags: int = 0):
         _batch_sigs()

@@ -1,5 +1,6 @@
-// Batches of nests: one persistent launch per kernel family, optionally replayed
-// from a hipGraph, and the one-launch-per-nest baseline over the same plans.
+// Batches of nests: one launch per kernel family (unit tasks, hp_units.hip, or persistent
+// workers over plans), optionally replayed from a hipGraph, and the one-launch-per-nest
+// baseline over the same plans.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -13,6 +14,7 @@
 #include "hp_batch_dev.h"
 #include "hp_fold.h"
 #include "hp_tune.h"
+#include "hp_units_dev.h"
 
 namespace hp {
 
@@ -121,33 +123,6 @@ hp_status warm_batch_kernels(hipStream_t st) {
   return HP_OK;
 }
 
-// The SimpleDesc of a plan, if it has that form (see hp_batch_dev.h).
-bool simple_desc_of(const DevPlan& P, SimpleDesc* D) {
-  if (P.dtype != HP_F32 && P.dtype != HP_BF16) return false;
-  const int c = P.dtype == HP_BF16 ? 8 : 4;
-  if (P.depth != 2 || P.p != 1 || P.nseg != 1 || P.seg[0].op != HP_OP_SUM || P.gmode != GCOMB_NONE) return false;
-  const DevLevel& L0 = P.lv[0];
-  const DevLevel& L1 = P.lv[1];
-  if (L1.gf != 1 || L1.wf != 1 || L1.vsh != 0 || L1.chunk != c || L1.ragged || L1.stride != 1) return false;
-  if (L0.wf != 1 || L0.chunk != 1 || L0.ostride != 1 || (L0.vf > 1 && (1 << L0.vsh) != L1.vf)) return false;
-  const int64_t lim = 0x7fffffffLL;
-  if (L0.e > lim || L0.strips > lim || L1.strips > lim || L0.stride > lim || P.flat_b > lim) return false;
-  if (L0.gdiv != 1 || (int64_t)L0.gf != P.grid) return false;
-  memset(D, 0, sizeof *D);
-  D->block = (int32_t)L0.stride;
-  D->flat_b = (int32_t)P.flat_b;
-  D->flat_e = (int32_t)P.flat_e;
-  D->e0 = (int32_t)L0.e;
-  D->g0 = (int32_t)L0.gf;
-  D->v0 = L0.vf;
-  D->v1 = L1.vf;
-  D->strips1 = (int32_t)L1.strips;
-  D->strips0 = (int32_t)L0.strips;
-  D->bits = (uint32_t)(L0.vf > 1 ? L0.vsh : 0) | (P.out_kind == OUT_F64 ? 0x100u : 0u) |
-            ((P.seg[0].ufast & 0x3Fu) << 16);
-  return true;
-}
-
 void deal_tasks(const int2* ordered, const double* weight, int n, int grid, int2* out, BatchArgs* B) {
   const int nq = grid < kQueues ? (grid < 1 ? 1 : grid) : kQueues;
   // queue q is served by the workgroups b < grid with b % kQueues == q; a task goes
@@ -198,9 +173,13 @@ hp_status launch_single(const DevPlan& P, const DevPlan* dP, const void* in, voi
 
 namespace {
 
-struct Group {  // nests of one kernel family and chunk: one persistent launch
+// Nests on unit tasks form one group per input type: family kUnitFamily + type, chunk 0.
+constexpr int kUnitFamily = hp::FAM_COUNT;
+
+struct Group {  // nests of one kernel family and chunk: one launch
   int family, chunk;
   long long n_tasks;
+  const int2* tasks;   // unit groups
   hp::BatchArgs args;  // pointers into the batch's device memory
   int grid;
   size_t lds;
@@ -227,9 +206,13 @@ struct hp_batch_s {
   hp::FoldTask* d_fold = nullptr;  // in the arena
   int n_fold = 0;
   std::vector<int> fold_beg;      // nest i's fold tasks: [fold_beg[i], fold_beg[i + 1])
-  std::vector<hp::SimpleDesc> simple;  // host copy of the compact descriptors (pointers set by set_io)
-  std::vector<char> is_simple;
-  hp::SimpleDesc* d_simple = nullptr;  // in the arena
+  std::vector<hp::UnitRoute> routes;
+  std::vector<hp::UnitDesc> units;      // host copy of the unit descriptors (pointers set by set_io)
+  hp::UnitDesc* d_units = nullptr;      // in the arena
+  int2* d_unit_folds = nullptr;         // in the arena
+  std::vector<int> unit_fold_beg;       // nest i's: [unit_fold_beg[i], unit_fold_beg[i + 1])
+  int n_unit_fold = 0;
+  int n_plan_groups = 0;                // groups with task counters
   bool io_set = false;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -253,7 +236,9 @@ static void batch_free(hp_batch_s* b) {
 namespace hp {
 
 // Build a batch from plans made by the caller (batched plans: kBatchWaves waves).
-hp_status batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags, hp_batch_s** out);
+// routes[i].on: nest i runs as unit tasks.
+hp_status batch_from_plans(const std::vector<Lowered>& plans, const std::vector<UnitRoute>& routes, uint32_t flags,
+                           hp_batch_s** out);
 
 }  // namespace hp
 
@@ -264,16 +249,19 @@ extern "C" hp_status hp_batch_plan(const hp_nest* nests, int64_t n, uint32_t fla
   if (flags & ~(uint32_t)(HP_BATCH_GRAPH | HP_FLAG_OUT_F32 | HP_BATCH_NO_TUNE))
     return fail(HP_EINVAL, "unknown batch flag bits 0x%x", flags);
   std::vector<Lowered> plans((size_t)n);
+  std::vector<UnitRoute> routes((size_t)n);
   const uint32_t pflags = flags & HP_FLAG_OUT_F32;
   for (int64_t i = 0; i < n; ++i) {
-    hp_status s = plan_for_batch(&nests[i], pflags, !(flags & HP_BATCH_NO_TUNE), kBatchWaves, &plans[(size_t)i]);
+    bool tuned = false;
+    hp_status s = plan_for_batch(&nests[i], pflags, !(flags & HP_BATCH_NO_TUNE), kBatchWaves, &plans[(size_t)i], &tuned);
     if (s != HP_OK) {
       char msg[512];
       snprintf(msg, sizeof msg, "%s", hp_last_error());
       return fail(s, "nest %lld: %s", (long long)i, msg);
     }
+    routes[(size_t)i] = unit_route(&nests[i], pflags, plans[(size_t)i], tuned);
   }
-  return batch_from_plans(plans, flags, out);
+  return batch_from_plans(plans, routes, flags, out);
 }
 
 extern "C" hp_status hp_batch_plan_inspect(const hp_nest* nests, int64_t n, uint32_t flags, hp_plan_info* infos) {
@@ -289,7 +277,8 @@ extern "C" hp_status hp_batch_plan_inspect(const hp_nest* nests, int64_t n, uint
   return HP_OK;
 }
 
-hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags, hp_batch_s** out) {
+hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vector<UnitRoute>& routes, uint32_t flags,
+                               hp_batch_s** out) {
   const int64_t n = (int64_t)plans.size();
   hp_batch_s* b = new (std::nothrow) hp_batch_s;
   if (!b) return fail(HP_ENOMEM, "host allocation failed");
@@ -313,6 +302,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
   for (int64_t i = 0; i < n; ++i) {
     const DevPlan& P = b->plans[(size_t)i];
     std::pair<int, int> k(family_of(P), P.chunk);
+    if (routes[(size_t)i].on) k = std::make_pair(kUnitFamily + P.dtype, 0);
     size_t g = 0;
     while (g < keys.size() && keys[g] != k) ++g;
     if (g == keys.size()) {
@@ -324,12 +314,16 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
   // device memory: plans, pointer tables, then one arena for tasks, counters and workspaces
   // the task counters of every group sit together at the start (zero after the
   // upload; each run leaves them at zero again), then each group's task list
-  size_t arena_bytes = align_up(keys.size() * kCtrWords * sizeof(unsigned int), 256);
+  b->routes = routes;
+  for (const auto& k : keys) b->n_plan_groups += k.first < kUnitFamily;
+  size_t arena_bytes = align_up((size_t)b->n_plan_groups * kCtrWords * sizeof(unsigned int), 256);
+  size_t n_ctr = 0;
   std::vector<size_t> task_off(keys.size()), ctr_off(keys.size());
   std::vector<long long> ntask(keys.size(), 0);
   for (size_t g = 0; g < keys.size(); ++g) {
-    for (int64_t i : members[g]) ntask[g] += b->plans[(size_t)i].grid;
-    ctr_off[g] = g * kCtrWords * sizeof(unsigned int);
+    const bool unit = keys[g].first >= kUnitFamily;
+    for (int64_t i : members[g]) ntask[g] += unit ? routes[(size_t)i].units : b->plans[(size_t)i].grid;
+    ctr_off[g] = (unit ? 0 : n_ctr++) * kCtrWords * sizeof(unsigned int);
     task_off[g] = arena_bytes;
     arena_bytes = align_up(arena_bytes + (size_t)ntask[g] * sizeof(int2), 256);
     if (ntask[g] > 0x7fffffffLL) {
@@ -337,22 +331,25 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
       return fail(HP_ETOOBIG, "batch group has %lld tasks, more than 2^31 - 1", ntask[g]);
     }
   }
-  // compact descriptors of the nests whose plans have the simple form (float
-  // families of depth <= 4 only: those kernels hold the simple path)
-  const size_t simple_off = arena_bytes;
-  arena_bytes = align_up(arena_bytes + (size_t)n * sizeof(SimpleDesc), 256);
-  std::vector<SimpleDesc> simple((size_t)n);
-  std::vector<char> is_simple((size_t)n, 0);
+  // the descriptors of the nests on unit tasks
+  const size_t unit_off = arena_bytes;
+  if (b->n_plan_groups < (int)keys.size()) arena_bytes = align_up(arena_bytes + (size_t)n * sizeof(UnitDesc), 256);
+  std::vector<int2> unit_folds;
+  b->unit_fold_beg.assign((size_t)n + 1, 0);
   for (int64_t i = 0; i < n; ++i) {
-    const DevPlan& P = b->plans[(size_t)i];
-    const int fam = family_of(P);
-    if ((fam == FAM_F32_4 || fam == FAM_BF16_4) && simple_desc_of(P, &simple[(size_t)i])) is_simple[(size_t)i] = 1;
+    b->unit_fold_beg[(size_t)i] = (int)unit_folds.size();
+    if (routes[(size_t)i].on)
+      for (int64_t o = 0; o < routes[(size_t)i].folds; ++o) unit_folds.push_back(make_int2((int)i, (int)o));
   }
+  b->unit_fold_beg[(size_t)n] = (int)unit_folds.size();
+  b->n_unit_fold = (int)unit_folds.size();
+  const size_t unit_fold_off = arena_bytes;
+  arena_bytes = align_up(arena_bytes + unit_folds.size() * sizeof(int2), 256);
   std::vector<hp::FoldTask> folds;
   b->fold_beg.assign((size_t)n + 1, 0);
   for (int64_t i = 0; i < n; ++i) {
     b->fold_beg[(size_t)i] = (int)folds.size();
-    fold_tasks_of(b->plans[(size_t)i], (int)i, folds);
+    if (!routes[(size_t)i].on) fold_tasks_of(b->plans[(size_t)i], (int)i, folds);
   }
   b->fold_beg[(size_t)n] = (int)folds.size();
   b->n_fold = (int)folds.size();
@@ -360,7 +357,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
   arena_bytes = align_up(arena_bytes + folds.size() * sizeof(hp::FoldTask), 256);
   std::vector<size_t> ws_off((size_t)n, 0);
   for (int64_t i = 0; i < n; ++i) {
-    const size_t wb = b->infos[(size_t)i].workspace_bytes;
+    const size_t wb = routes[(size_t)i].on ? (size_t)routes[(size_t)i].ws_bytes : b->infos[(size_t)i].workspace_bytes;
     if (wb) {
       ws_off[(size_t)i] = arena_bytes;
       arena_bytes = align_up(arena_bytes + wb, 256);
@@ -375,17 +372,38 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
   b->d_out = reinterpret_cast<void**>(const_cast<void**>(b->d_in + n));
   b->d_ws = reinterpret_cast<unsigned char**>(const_cast<void**>(b->d_in + 2 * n));
   std::vector<unsigned char> host_arena(arena_bytes, 0);
-  memcpy(host_arena.data() + simple_off, simple.data(), (size_t)n * sizeof(SimpleDesc));
-  b->d_simple = reinterpret_cast<SimpleDesc*>((unsigned char*)b->arena + simple_off);
-  b->simple.swap(simple);
-  b->is_simple.swap(is_simple);
+  b->d_units = reinterpret_cast<UnitDesc*>((unsigned char*)b->arena + unit_off);
+  b->d_unit_folds = reinterpret_cast<int2*>((unsigned char*)b->arena + unit_fold_off);
+  if (!unit_folds.empty()) memcpy(host_arena.data() + unit_fold_off, unit_folds.data(), unit_folds.size() * sizeof(int2));
   if (!folds.empty()) memcpy(host_arena.data() + fold_off, folds.data(), folds.size() * sizeof(hp::FoldTask));
   b->d_fold = reinterpret_cast<hp::FoldTask*>((unsigned char*)b->arena + fold_off);
   b->ws_ptrs.assign((size_t)n, nullptr);
   for (int64_t i = 0; i < n; ++i)
-    if (b->infos[(size_t)i].workspace_bytes) b->ws_ptrs[(size_t)i] = (unsigned char*)b->arena + ws_off[(size_t)i];
+    if (ws_off[(size_t)i]) b->ws_ptrs[(size_t)i] = (unsigned char*)b->arena + ws_off[(size_t)i];
+  if (b->n_plan_groups < (int)keys.size()) {
+    b->units.resize((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+      b->units[(size_t)i] = routes[(size_t)i].d;
+      b->units[(size_t)i].ws = b->ws_ptrs[(size_t)i];
+    }
+  }
   for (size_t g = 0; g < keys.size(); ++g) {
     std::vector<int64_t>& mem = members[g];
+    if (keys[g].first >= kUnitFamily) {  // a wave per unit, largest units first
+      std::stable_sort(mem.begin(), mem.end(), [&](int64_t x, int64_t y) {
+        return routes[(size_t)x].unit_bytes > routes[(size_t)y].unit_bytes;
+      });
+      int2* t = reinterpret_cast<int2*>(host_arena.data() + task_off[g]);
+      for (int64_t i : mem)
+        for (int64_t u = 0; u < routes[(size_t)i].units; ++u) *t++ = make_int2((int)i, (int)u);
+      Group G{};
+      G.family = keys[g].first;
+      G.n_tasks = ntask[g];
+      G.grid = (int)((ntask[g] + 3) / 4);
+      G.tasks = reinterpret_cast<const int2*>((unsigned char*)b->arena + task_off[g]);
+      b->groups.push_back(G);
+      continue;
+    }
     // largest work per task first
     std::stable_sort(mem.begin(), mem.end(), [&](int64_t a, int64_t c) {
       const double wa = (double)b->infos[(size_t)a].in_bytes / (double)b->plans[(size_t)a].grid;
@@ -399,7 +417,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
       const double wt = task_cost((double)b->infos[(size_t)i].in_bytes / (double)b->plans[(size_t)i].grid);
       for (long long w = 0; w < b->plans[(size_t)i].grid; ++w) {
         weight[(size_t)k] = wt;
-        ordered[(size_t)k++] = make_int2((int)i, (int)w | (b->is_simple[(size_t)i] ? kSimpleTask : 0));
+        ordered[(size_t)k++] = make_int2((int)i, (int)w);
       }
     }
     Group G;
@@ -420,7 +438,6 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags
     deal_tasks(ordered.data(), weight.data(), (int)ntask[g], G.grid,
                reinterpret_cast<int2*>(host_arena.data() + task_off[g]), &G.args);
     G.args.tasks = reinterpret_cast<const int2*>((unsigned char*)b->arena + task_off[g]);
-    G.args.simple = b->d_simple;
     G.args.ctr = reinterpret_cast<unsigned int*>((unsigned char*)b->arena + ctr_off[g]);
     b->groups.push_back(G);
   }
@@ -448,7 +465,7 @@ extern "C" hp_status hp_batch_stats(hp_batch_t b, int64_t* n_launches, int64_t* 
   long long t = 0, w = 0;
   for (const Group& g : b->groups) {
     t += g.n_tasks;
-    w += (long long)g.grid * hp::kBatchGroupWaves;
+    w += g.family >= kUnitFamily ? g.n_tasks : (long long)g.grid * hp::kBatchGroupWaves;
   }
   if (n_launches) *n_launches = (int64_t)b->groups.size();
   if (n_tasks) *n_tasks = t;
@@ -474,17 +491,14 @@ extern "C" hp_status hp_batch_set_io(hp_batch_t b, const void* const* d_in, void
     b->exec_each = nullptr;
     b->graph_each = nullptr;
   }
-  bool any_simple = false;
-  for (int64_t i = 0; i < b->n; ++i)
-    if (b->is_simple[(size_t)i]) {
-      b->simple[(size_t)i].in = d_in[i];
-      b->simple[(size_t)i].out = d_out[i];
-      any_simple = true;
-    }
+  for (size_t i = 0; i < b->units.size(); ++i) {
+    b->units[i].in = d_in[i];
+    b->units[i].out = d_out[i];
+  }
   if (hipMemcpy(b->d_in, d_in, sizeof(void*) * (size_t)b->n, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(b->d_out, d_out, sizeof(void*) * (size_t)b->n, hipMemcpyHostToDevice) != hipSuccess ||
-      (any_simple && hipMemcpy(b->d_simple, b->simple.data(), sizeof(hp::SimpleDesc) * (size_t)b->n,
-                               hipMemcpyHostToDevice) != hipSuccess))
+      (!b->units.empty() && hipMemcpy(b->d_units, b->units.data(), sizeof(hp::UnitDesc) * b->units.size(),
+                                      hipMemcpyHostToDevice) != hipSuccess))
     return hp::fail(HP_EDEVICE, "pointer table upload failed");
   b->io_set = true;
   return HP_OK;
@@ -492,6 +506,11 @@ extern "C" hp_status hp_batch_set_io(hp_batch_t b, const void* const* d_in, void
 
 static hp_status launch_groups(hp_batch_s* b, hipStream_t st) {
   for (const Group& G : b->groups) {
+    if (G.family >= kUnitFamily) {
+      const hp_status s = hp::launch_units(G.family - kUnitFamily, b->d_units, G.tasks, (int)G.n_tasks, st);
+      if (s != HP_OK) return s;
+      continue;
+    }
     hp::BatchArgs A = G.args;
     A.plans = b->d_plans;
     A.ins = b->d_in;
@@ -503,9 +522,10 @@ static hp_status launch_groups(hp_batch_s* b, hipStream_t st) {
     if (s == HP_OK) s = hp::launch_batch(G.family, G.chunk, A, G.grid, hp::kBatchGroupWaves, G.lds, st);
     if (s != HP_OK) return s;
   }
-  if (b->n_fold <= 0) return HP_OK;
+  const hp_status s = hp::launch_unit_folds(b->d_units, b->d_unit_folds, b->n_unit_fold, st);
+  if (s != HP_OK || b->n_fold <= 0) return s;
   return hp::launch_fold(b->d_plans, b->d_fold, b->n_fold, b->d_out, b->d_ws, st,
-                         reinterpret_cast<unsigned int*>(b->arena), (int)(b->groups.size() * hp::kCtrWords));
+                         reinterpret_cast<unsigned int*>(b->arena), b->n_plan_groups * hp::kCtrWords);
 }
 
 static hp_status capture(hp_batch_s* b, bool each, hipGraph_t* graph, hipGraphExec_t* exec);
@@ -528,8 +548,18 @@ extern "C" hp_status hp_batch_run(hp_batch_t b, void* stream) {
   return launch_groups(b, st);
 }
 
-// The fold kernel of nest i alone (what hp_run launches after a grid-split nest).
+// Nest i alone: its unit tasks, or its plan's kernel.
+static hp_status launch_one(hp_batch_s* b, int64_t i, const void* in, void* out, hipStream_t st) {
+  if (b->routes[(size_t)i].on)
+    return hp::launch_units_of(b->routes[(size_t)i].dtype, b->d_units + i, (int)b->routes[(size_t)i].units, st);
+  return hp::launch_single(b->plans[(size_t)i], b->d_plans + i, in, out, b->ws_ptrs[(size_t)i],
+                           b->infos[(size_t)i].lds_bytes, st);
+}
+
+// The fold of nest i alone.
 static hp_status launch_fold_of(hp_batch_s* b, int64_t i, hipStream_t st) {
+  const int u0 = b->unit_fold_beg[(size_t)i], u1 = b->unit_fold_beg[(size_t)i + 1];
+  if (u1 > u0) return hp::launch_unit_folds(b->d_units, b->d_unit_folds + u0, u1 - u0, st);
   const int f0 = b->fold_beg[(size_t)i], f1 = b->fold_beg[(size_t)i + 1];
   if (f1 == f0) return HP_OK;
   return hp::launch_fold(b->d_plans, b->d_fold + f0, f1 - f0, b->d_out, b->d_ws, st);
@@ -544,8 +574,7 @@ static hp_status launch_each(hp_batch_s* b, hipStream_t st) {
       hipMemcpy(out.data(), b->d_out, sizeof(void*) * (size_t)b->n, hipMemcpyDeviceToHost) != hipSuccess)
     return hp::fail(HP_EDEVICE, "pointer table download failed");
   for (int64_t i = 0; i < b->n; ++i) {
-    hp_status s = hp::launch_single(b->plans[(size_t)i], b->d_plans + i, in[(size_t)i], out[(size_t)i],
-                                    b->ws_ptrs[(size_t)i], b->infos[(size_t)i].lds_bytes, st);
+    hp_status s = launch_one(b, i, in[(size_t)i], out[(size_t)i], st);
     if (s == HP_OK) s = launch_fold_of(b, i, st);
     if (s != HP_OK) return s;
   }
@@ -571,8 +600,7 @@ static hp_status capture(hp_batch_s* b, bool each, hipGraph_t* graph, hipGraphEx
       return hp::fail(HP_EDEVICE, "begin capture failed");
     }
     for (int64_t i = 0; i < b->n && s == HP_OK; ++i) {
-      s = hp::launch_single(b->plans[(size_t)i], b->d_plans + i, ins[(size_t)i], outs[(size_t)i],
-                            b->ws_ptrs[(size_t)i], b->infos[(size_t)i].lds_bytes, cs);
+      s = launch_one(b, i, ins[(size_t)i], outs[(size_t)i], cs);
       if (s == HP_OK) s = launch_fold_of(b, i, cs);
     }
   } else {

@@ -1007,7 +1007,7 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
     op[ns] = n->op[l];
     e[ns++] = n->extent[l];
   }
-  if (ns < 2 || (ns == 3 && e[0] == 1)) return off;  // (an ARG level of one iteration outside: always 0)
+  if (ns < 2) return off;
   const int64_t lim = (int64_t)1 << 30;
   if (e[ns - 1] >= lim || e[ns - 2] >= lim || (ns == 3 && e[0] >= lim)) return off;
   S.opL = op[ns - 1];
@@ -1072,7 +1072,7 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
     S.run = (int32_t)cdiv(groups, want);
     S.grid = (uint32_t)cdiv(cdiv(groups, S.run), 4);
   }
-  S.tail = (S.eQ > 1 || parts > 1) ? 1 : 0;
+  S.tail = (ns == 3 || parts > 1) ? 1 : 0;
   if (S.tail && parts == 1 && (int64_t)S.eM * S.eL < 8) return off;  // the carriers would outweigh the input
   S.ws_bytes = S.tail ? (uint64_t)S.units * kSlotBytes : 0;
   S.kind = SEGS_SHORT;

@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(1024) k_seg_tail(const In* __restrict__ ws, vo
   };
   IAcc r;
   int op;
-  if (eQ == 1) {  // M alone: the whole workgroup on its entries
+  if (opQ == HP_OP_NONE) {  // M alone: the whole workgroup on its entries
     r = span(p, (int)threadIdx.x, (int)blockDim.x);
     op = opM;
   } else if (n <= 8) {  // few entries per q: a lane per q
@@ -380,10 +380,10 @@ __global__ void __launch_bounds__(256) k_seg_tail_lane(const In* __restrict__ ws
       if constexpr (PARTS) a = IntT::merge(a, p[(long long)q * n + m], opM);
       else outer_add(a, (long long)p[(long long)q * n + m], m, opM, true);
     }
-    if (eQ == 1) r = a;
+    if (opQ == HP_OP_NONE) r = a;
     else outer_add(r, IntT::emit(a, opM), q, opQ, true);
   }
-  const long long v = IntT::emit(r, eQ == 1 ? opM : opQ);
+  const long long v = IntT::emit(r, opQ == HP_OP_NONE ? opM : opQ);
   if (out64) reinterpret_cast<long long*>(out)[o] = v;
   else reinterpret_cast<int*>(out)[o] = (int)v;
 }

@@ -35,8 +35,10 @@ Recipe default_recipe(const hp_nest* nest, int nw);
 std::string tune_key(const hp_nest* nest);
 
 // Plan one nest of a batch: the tuned map of its class if the cache has one and
-// use_tuner is set, else the automatic map; always `nw` waves per workgroup.
-hp_status plan_for_batch(const hp_nest* nest, uint32_t flags, bool use_tuner, int nw, Lowered* out);
+// use_tuner is set (then *tuned is true), else the automatic map; always `nw` waves per
+// workgroup.
+hp_status plan_for_batch(const hp_nest* nest, uint32_t flags, bool use_tuner, int nw, Lowered* out,
+                         bool* tuned = nullptr);
 
 // Build the nest and map a recipe stands for (false if the recipe does not apply).
 // *flat_block receives 0, or the block length when `shaped` is the aligned interior

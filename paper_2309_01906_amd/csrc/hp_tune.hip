@@ -17,10 +17,12 @@
 #include "hp_internal.h"
 #include "hp_batch_dev.h"
 #include "hp_tune.h"
+#include "hp_units.h"
 
 struct hp_batch_s;
 namespace hp {
-hp_status batch_from_plans(const std::vector<Lowered>& plans, uint32_t flags, hp_batch_s** out);
+hp_status batch_from_plans(const std::vector<Lowered>& plans, const std::vector<UnitRoute>& routes, uint32_t flags,
+                           hp_batch_s** out);
 }
 
 namespace {
@@ -193,19 +195,24 @@ Recipe default_recipe(const hp_nest* n, int nw) {
   return r;
 }
 
-hp_status plan_for_batch(const hp_nest* nest, uint32_t flags, bool use_tuner, int nw, Lowered* out) {
+hp_status plan_for_batch(const hp_nest* nest, uint32_t flags, bool use_tuner, int nw, Lowered* out, bool* tuned) {
+  if (tuned) *tuned = false;
   if (!nest) return fail(HP_EINVAL, "null nest");
   Recipe r = default_recipe(nest, nw);
   if (use_tuner) {
     std::lock_guard<std::mutex> lk(g_mu);
     load_env_locked();
     auto it = g_cache.find(tune_key(nest));
-    if (it != g_cache.end()) r = it->second;
+    if (it != g_cache.end()) {
+      r = it->second;
+      if (tuned) *tuned = r.mode != 0;
+    }
   }
   hp_nest shaped;
   hp_level_map m;
   int64_t fb = 0;
   if (apply_recipe(nest, r, nw, &shaped, &m, &fb) && lower(&shaped, &m, flags, out, nw, fb) == HP_OK) return HP_OK;
+  if (tuned) *tuned = false;
   return lower(nest, nullptr, flags, out, nw);
 }
 
@@ -255,13 +262,15 @@ struct Timed {
 };
 
 // Throughput of a candidate inside a batch: R replicas of the plan (distinct input
-// and output slots) as one persistent launch; returns the median time per nest.
+// and output slots) as one launch; returns the median time per nest.
 // This is the figure that matters when the nest shares the device with others.
-hp_status time_candidate_batch(const hp::Lowered& L, int R, unsigned char* in, size_t in_stride, unsigned char* out,
-                               size_t out_stride, int reps, hipStream_t st, double* us) {
+hp_status time_candidate_batch(const hp::Lowered& L, const hp::UnitRoute& route, int R, unsigned char* in,
+                               size_t in_stride, unsigned char* out, size_t out_stride, int reps, hipStream_t st,
+                               double* us) {
   std::vector<hp::Lowered> plans((size_t)R, L);
   hp_batch_s* b = nullptr;
-  hp_status s = hp::batch_from_plans(plans, 0, &b);
+  const std::vector<hp::UnitRoute> routes((size_t)R, route);
+  hp_status s = hp::batch_from_plans(plans, routes, 0, &b);
   if (s != HP_OK) return s;
   std::vector<const void*> ins((size_t)R);
   std::vector<void*> outs((size_t)R);
@@ -325,7 +334,7 @@ extern "C" hp_status hp_tune_nest(const hp_nest* nest, uint32_t flags, int32_t r
     return fail(HP_EDEVICE, "tuner stream");
   }
   double t_auto = 0;
-  s = time_candidate_batch(L0, R, in, in_stride, out, out_stride, reps, st, &t_auto);
+  s = time_candidate_batch(L0, unit_route(nest, flags, L0, false), R, in, in_stride, out, out_stride, reps, st, &t_auto);
   Recipe best{0, 0, 1, 1, 64, 1, t_auto};
   auto consider = [&](const Recipe& r) {
     hp_nest shaped;
@@ -335,7 +344,8 @@ extern "C" hp_status hp_tune_nest(const hp_nest* nest, uint32_t flags, int32_t r
     if (!apply_recipe(nest, r, kBatchWaves, &shaped, &m, &fb)) return;
     if (lower(&shaped, &m, flags, &L, kBatchWaves, fb) != HP_OK) return;
     double us = 0;
-    if (time_candidate_batch(L, R, in, in_stride, out, out_stride, reps, st, &us) != HP_OK) return;
+    if (time_candidate_batch(L, unit_route(nest, flags, L, true), R, in, in_stride, out, out_stride, reps, st, &us) != HP_OK)
+      return;
     if (us < best.us * 0.98) {
       best = r;
       best.us = us;

@@ -1,0 +1,56 @@
+// Unit tasks of batches and the server: nests of one to three reducing segments as
+// independent pieces of a wavefront's work (hp_units.hip; the partition is made by
+// unit_route in hp_units.cpp).
+#pragma once
+
+#include <stdint.h>
+
+#include "hp_internal.h"
+
+namespace hp {
+
+enum UnitOut : int32_t { UNIT_F64 = 0, UNIT_F32, UNIT_I64, UNIT_I32 };
+
+// A nest as unit tasks.  The view is that of the segment kernels: out[o] = Q over q of M
+// over m of L over the contiguous row (o, q, m); a single reduction has M and Q of one
+// iteration.  Unit u is one of
+//   a run of groups of 2^pair_bits (o, q) pairs side by side   (mparts = lparts = 1),
+//   steps [per part, per (part + 1)) of pair u / mparts         (part = u % mparts),
+//   elements [part_len part, ...) of row u / lparts             (part = u % lparts).
+// With `partial` a unit leaves carriers of M (or, split rows, of L) in ws and a fold task
+// per output ends the nest.
+struct alignas(128) UnitDesc {
+  const void* in;
+  void* out;
+  unsigned char* ws;
+  int64_t pairs;
+  int32_t eL, eM, eQ;
+  int32_t opL, opM, opQ;
+  int32_t vecs;       // vectors per lane of a row (0: rows shorter than a vector)
+  int32_t lane_bits;  // 2^lane_bits lanes per row
+  int32_t pair_bits;
+  int32_t steps;      // steps of a pair
+  int32_t run;        // groups per unit
+  int32_t mparts, per;
+  int32_t lparts, part_len;
+  int32_t out_kind;   // UnitOut
+  int32_t partial;
+  int32_t direct;     // one segment: a row's value is an output
+};
+static_assert(sizeof(UnitDesc) == 128, "one descriptor is one 128-byte line");
+
+struct UnitRoute {
+  int32_t on;        // 0: the nest runs as the plan's own tasks
+  int32_t dtype;
+  UnitDesc d;        // pointers unset
+  int64_t units;
+  int64_t folds;     // fold tasks
+  uint64_t ws_bytes;
+  double unit_bytes; // input bytes of the largest unit, for the order of the tasks
+};
+
+// The unit route of a batched nest whose plan is L.  tuned: L comes from the tuner cache,
+// whose grid (units per output or outputs per unit) and lanes per output are kept.
+UnitRoute unit_route(const hp_nest* nest, uint32_t flags, const Lowered& L, bool tuned);
+
+}  // namespace hp

@@ -1,0 +1,17 @@
+// Launchers of the unit kernels.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "hp_units.h"
+
+namespace hp {
+
+// n unit tasks (nest, unit) of nests of one input type, a wave each, in list order.
+hp_status launch_units(int dtype, const UnitDesc* descs, const int2* tasks, int n, hipStream_t st);
+// All units of one nest (n of them), in order: the baseline of one launch per nest.
+hp_status launch_units_of(int dtype, const UnitDesc* desc, int n, hipStream_t st);
+// The nests' partial carriers: n fold tasks (nest, output), a wave each.
+hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n, hipStream_t st);
+
+}  // namespace hp
