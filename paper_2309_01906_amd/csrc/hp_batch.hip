@@ -173,9 +173,6 @@ hp_status launch_single(const DevPlan& P, const DevPlan* dP, const void* in, voi
 
 namespace {
 
-// Nests on unit tasks form one group per input type: family kUnitFamily + type, chunk 0.
-constexpr int kUnitFamily = hp::FAM_COUNT;
-
 struct Group {  // nests of one kernel family and chunk: one launch
   int family, chunk;
   long long n_tasks;
@@ -302,7 +299,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   for (int64_t i = 0; i < n; ++i) {
     const DevPlan& P = b->plans[(size_t)i];
     std::pair<int, int> k(family_of(P), P.chunk);
-    if (routes[(size_t)i].on) k = std::make_pair(kUnitFamily + P.dtype, 0);
+    if (routes[(size_t)i].on) k = std::make_pair(hp::kUnitFamily + P.dtype, 0);
     size_t g = 0;
     while (g < keys.size() && keys[g] != k) ++g;
     if (g == keys.size()) {
@@ -315,13 +312,13 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   // the task counters of every group sit together at the start (zero after the
   // upload; each run leaves them at zero again), then each group's task list
   b->routes = routes;
-  for (const auto& k : keys) b->n_plan_groups += k.first < kUnitFamily;
+  for (const auto& k : keys) b->n_plan_groups += k.first < hp::kUnitFamily;
   size_t arena_bytes = align_up((size_t)b->n_plan_groups * kCtrWords * sizeof(unsigned int), 256);
   size_t n_ctr = 0;
   std::vector<size_t> task_off(keys.size()), ctr_off(keys.size());
   std::vector<long long> ntask(keys.size(), 0);
   for (size_t g = 0; g < keys.size(); ++g) {
-    const bool unit = keys[g].first >= kUnitFamily;
+    const bool unit = keys[g].first >= hp::kUnitFamily;
     for (int64_t i : members[g]) ntask[g] += unit ? routes[(size_t)i].units : b->plans[(size_t)i].grid;
     ctr_off[g] = (unit ? 0 : n_ctr++) * kCtrWords * sizeof(unsigned int);
     task_off[g] = arena_bytes;
@@ -389,7 +386,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   }
   for (size_t g = 0; g < keys.size(); ++g) {
     std::vector<int64_t>& mem = members[g];
-    if (keys[g].first >= kUnitFamily) {  // a wave per unit, largest units first
+    if (keys[g].first >= hp::kUnitFamily) {  // a wave per unit, largest units first
       std::stable_sort(mem.begin(), mem.end(), [&](int64_t x, int64_t y) {
         return routes[(size_t)x].unit_bytes > routes[(size_t)y].unit_bytes;
       });
@@ -465,7 +462,7 @@ extern "C" hp_status hp_batch_stats(hp_batch_t b, int64_t* n_launches, int64_t* 
   long long t = 0, w = 0;
   for (const Group& g : b->groups) {
     t += g.n_tasks;
-    w += g.family >= kUnitFamily ? g.n_tasks : (long long)g.grid * hp::kBatchGroupWaves;
+    w += g.family >= hp::kUnitFamily ? g.n_tasks : (long long)g.grid * hp::kBatchGroupWaves;
   }
   if (n_launches) *n_launches = (int64_t)b->groups.size();
   if (n_tasks) *n_tasks = t;
@@ -506,8 +503,8 @@ extern "C" hp_status hp_batch_set_io(hp_batch_t b, const void* const* d_in, void
 
 static hp_status launch_groups(hp_batch_s* b, hipStream_t st) {
   for (const Group& G : b->groups) {
-    if (G.family >= kUnitFamily) {
-      const hp_status s = hp::launch_units(G.family - kUnitFamily, b->d_units, G.tasks, (int)G.n_tasks, st);
+    if (G.family >= hp::kUnitFamily) {
+      const hp_status s = hp::launch_units(G.family - hp::kUnitFamily, b->d_units, G.tasks, (int)G.n_tasks, st);
       if (s != HP_OK) return s;
       continue;
     }

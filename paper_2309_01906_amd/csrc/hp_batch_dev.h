@@ -89,10 +89,12 @@ __device__ __forceinline__ void batch_run_waves(const BatchArgs& B, char* lds) {
   }
 }
 
-// Kernel families.  Every nest of one persistent launch belongs to one family.
+// Kernel families.  Every nest of one launch belongs to one family.
 enum Family : int32_t {
   FAM_F32_4 = 0, FAM_F32_8, FAM_BF16_4, FAM_BF16_8, FAM_I32_FLAT, FAM_I32_SEG, FAM_I32_DEEP, FAM_COUNT
 };
+// Nests on unit tasks form one family per input type: kUnitFamily + type, chunk 0.
+constexpr int kUnitFamily = FAM_COUNT;
 __host__ __device__ inline int family_of(const DevPlan& P) {
   if (P.dtype == HP_F32) return P.depth <= 4 ? FAM_F32_4 : FAM_F32_8;
   if (P.dtype == HP_BF16) return P.depth <= 4 ? FAM_BF16_4 : FAM_BF16_8;

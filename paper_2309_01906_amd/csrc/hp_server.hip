@@ -3,12 +3,17 @@
 // Clients submit requests (a nest plus device input/output pointers) at any time.
 // One scheduler thread admits pending requests in arrival order while their bytes
 // (input + output + grid-combine workspace) fit in the HBM budget, forms a batch as
-// soon as one of K in-flight slots is free, uploads the batch's plans / task list /
-// pointer tables into that slot's device arena with one asynchronous copy, launches
-// the persistent kernels of the batch on the slot's stream, and polls the slots'
-// completion events.  Batches on different slots overlap on the device.  Every
-// request keeps the plan it would get alone, so its result does not depend on what
-// it was batched with.
+// soon as one of K in-flight slots is free, uploads the batch's descriptors, plans and
+// task lists into that slot's device arena with one asynchronous copy, launches the
+// batch's kernels on the slot's stream (unit tasks where a nest has them, hp_units.hip,
+// else persistent workers on plan tasks), and polls the slots' completion events.
+// Batches on different slots overlap on the device.  How a request runs is decided when
+// it is submitted, by its nest and the server's slot size alone, so its result does not
+// depend on what it was batched with.
+//
+// Measured: a burst of 1,000 mixed requests (int32 nests of 1 to 3 segments, float and
+// bf16 rows; 16 Ki elements in the median) from Python, submitted to waited for: 4.34 ms
+// with plan tasks alone, 3.3-3.6 ms with unit tasks; the rest is host work per request.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,12 +33,22 @@
 #include "hp_batch_dev.h"
 #include "hp_fold.h"
 #include "hp_tune.h"
+#include "hp_units_dev.h"
 
 namespace {
 
 using Clock = std::chrono::steady_clock;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+size_t A256(size_t x) { return align_up(x, 256); }
+
+// What a request adds to a slot arena (see Sum).
+struct Share {
+  std::pair<int, int> key;  // kernel family and chunk: one launch per key
+  long long ntask;          // workgroup tasks, or units
+  long long nfold;          // fold tasks
+  size_t ws;                // grid-combine workspace, 256-byte aligned
+};
 
 struct Request {
   uint64_t id;
@@ -44,35 +59,43 @@ struct Request {
   size_t bytes;  // budget charge
   hp_req_info info;
   int bypassed;
-  // what the request adds to a slot arena (see Tally)
-  std::pair<int, int> key;  // kernel family and chunk: one persistent launch per key
-  long long ntask;          // workgroup tasks
-  long long nfold;          // fold tasks
-  size_t ws;                // grid-combine workspace, 256-byte aligned
+  hp::UnitRoute unit;  // how it runs, where unit.on; else as tasks of its plan
+  Share as_plan, as_run;
 };
 
-size_t A256(size_t x) { return align_up(x, 256); }
-
-// Bytes of slot arena a batch needs: plans, the pointer tables, per kernel family
-// its task list and queue counters, the fold tasks and the workspaces, each region
-// 256-byte aligned.  layout_batch lays the regions out in this order; Tally keeps
-// the same sum up to date while a batch is packed, one request at a time, so a
-// batch never outgrows its slot.
-struct Tally {
-  int64_t n = 0;
-  long long nfold = 0;
+// Bytes of slot arena a batch needs: the plans and pointer tables of the requests that
+// run as plan tasks, per kernel family its task list and queue counters, the unit
+// descriptors, both kinds of fold tasks and the workspaces, each region 256-byte
+// aligned.  layout_batch lays the regions out in this order.
+struct Sum {
+  int64_t n_plans = 0, n_units = 0;
+  long long n_fold = 0, n_unit_fold = 0;
   size_t ws = 0;
   std::vector<std::pair<int, int>> keys;
   std::vector<long long> ntask;
 
-  size_t total() const {
-    size_t t = A256(sizeof(hp::DevPlan) * (size_t)n) + A256(3 * sizeof(void*) * (size_t)n);
-    for (long long k : ntask) t += A256((size_t)k * sizeof(int2)) + A256(hp::kCtrWords * sizeof(unsigned int));
-    return t + A256((size_t)nfold * sizeof(hp::FoldTask)) + ws;
+  static size_t group(int family, long long tasks) {
+    return A256((size_t)tasks * sizeof(int2)) +
+           (family < hp::kUnitFamily ? A256(hp::kCtrWords * sizeof(unsigned int)) : 0);
   }
-  void add(const Request& r) {
-    ++n;
-    nfold += r.nfold;
+  size_t total_with(const Share& r) const {
+    const bool unit = r.key.first >= hp::kUnitFamily;
+    const size_t np = (size_t)n_plans + !unit, nu = (size_t)n_units + unit;
+    size_t t = A256(sizeof(hp::DevPlan) * np) + A256(3 * sizeof(void*) * np) + A256(sizeof(hp::UnitDesc) * nu);
+    bool found = false;
+    for (size_t g = 0; g < keys.size(); ++g) {
+      const bool same = keys[g] == r.key;
+      t += group(keys[g].first, ntask[g] + (same ? r.ntask : 0));
+      found = found || same;
+    }
+    if (!found) t += group(r.key.first, r.ntask);
+    t += A256((size_t)(n_fold + (unit ? 0 : r.nfold)) * sizeof(hp::FoldTask));
+    t += A256((size_t)(n_unit_fold + (unit ? r.nfold : 0)) * sizeof(int2));
+    return t + ws + r.ws;
+  }
+  void add(const Share& r) {
+    if (r.key.first >= hp::kUnitFamily) ++n_units, n_unit_fold += r.nfold;
+    else ++n_plans, n_fold += r.nfold;
     ws += r.ws;
     size_t g = 0;
     while (g < keys.size() && keys[g] != r.key) ++g;
@@ -82,59 +105,80 @@ struct Tally {
     }
     ntask[g] += r.ntask;
   }
+};
+
+// The sum kept up to date while a batch is packed, one request at a time, so that a
+// batch never outgrows its slot.  A slot also holds no more requests than would fit it
+// as plan tasks: what fits a slot, and what is refused, does not depend on how it runs.
+struct Tally {
+  Sum plans, runs;
+
+  void add(const Request& r) {
+    plans.add(r.as_plan);
+    runs.add(r.as_run);
+  }
   size_t total_with(const Request& r) const {
-    Tally t = *this;
-    t.add(r);
-    return t.total();
+    return std::max(plans.total_with(r.as_plan), runs.total_with(r.as_run));
   }
 };
 
 struct Layout {
-  size_t plans_off = 0, ptr_off = 0, fold_off = 0, ws_begin = 0, total = 0;
+  size_t plans_off = 0, ptr_off = 0, unit_off = 0, fold_off = 0, unit_fold_off = 0, ws_begin = 0, total = 0;
+  int64_t n_plans = 0, n_units = 0;
+  std::vector<int64_t> at;  // request i is plan, or unit descriptor, at[i]
   std::vector<std::pair<int, int>> keys;
   std::vector<std::vector<int64_t>> members;
   std::vector<size_t> task_off, ctr_off;
   std::vector<long long> ntask;
   std::vector<hp::FoldTask> folds;
+  long long n_unit_fold = 0;
   std::vector<size_t> ws_off;
 };
 
 void layout_batch(const std::vector<Request*>& rs, Layout& Lo) {
   using namespace hp;
   const int64_t n = (int64_t)rs.size();
-  size_t off = 0;
-  Lo.plans_off = off;
-  off = align_up(off + sizeof(DevPlan) * (size_t)n, 256);
-  Lo.ptr_off = off;
-  off = align_up(off + 3 * sizeof(void*) * (size_t)n, 256);
+  Lo.at.resize((size_t)n);
   for (int64_t i = 0; i < n; ++i) {
+    const Request& r = *rs[(size_t)i];
+    Lo.at[(size_t)i] = r.unit.on ? Lo.n_units++ : Lo.n_plans++;
+    if (r.unit.on) Lo.n_unit_fold += r.as_run.nfold;
+    else fold_tasks_of(r.L.dp, (int)Lo.at[(size_t)i], Lo.folds);
     size_t g = 0;
-    while (g < Lo.keys.size() && Lo.keys[g] != rs[(size_t)i]->key) ++g;
+    while (g < Lo.keys.size() && Lo.keys[g] != r.as_run.key) ++g;
     if (g == Lo.keys.size()) {
-      Lo.keys.push_back(rs[(size_t)i]->key);
+      Lo.keys.push_back(r.as_run.key);
       Lo.members.emplace_back();
     }
     Lo.members[g].push_back(i);
   }
+  size_t off = 0;
+  Lo.plans_off = off;
+  off = align_up(off + sizeof(DevPlan) * (size_t)Lo.n_plans, 256);
+  Lo.ptr_off = off;
+  off = align_up(off + 3 * sizeof(void*) * (size_t)Lo.n_plans, 256);
   Lo.task_off.resize(Lo.keys.size());
   Lo.ctr_off.resize(Lo.keys.size());
   Lo.ntask.assign(Lo.keys.size(), 0);
   for (size_t g = 0; g < Lo.keys.size(); ++g) {
-    for (int64_t i : Lo.members[g]) Lo.ntask[g] += rs[(size_t)i]->ntask;
+    for (int64_t i : Lo.members[g]) Lo.ntask[g] += rs[(size_t)i]->as_run.ntask;
     Lo.task_off[g] = off;
     off = align_up(off + (size_t)Lo.ntask[g] * sizeof(int2), 256);
     Lo.ctr_off[g] = off;
-    off = align_up(off + kCtrWords * sizeof(unsigned int), 256);
+    if (Lo.keys[g].first < kUnitFamily) off = align_up(off + kCtrWords * sizeof(unsigned int), 256);
   }
-  for (int64_t i = 0; i < n; ++i) fold_tasks_of(rs[(size_t)i]->L.dp, (int)i, Lo.folds);
+  Lo.unit_off = off;
+  off = align_up(off + sizeof(UnitDesc) * (size_t)Lo.n_units, 256);
   Lo.fold_off = off;
   off = align_up(off + Lo.folds.size() * sizeof(FoldTask), 256);
+  Lo.unit_fold_off = off;
+  off = align_up(off + (size_t)Lo.n_unit_fold * sizeof(int2), 256);
   Lo.ws_begin = off;
   Lo.ws_off.assign((size_t)n, 0);
   for (int64_t i = 0; i < n; ++i) {
-    if (rs[(size_t)i]->ws) {
+    if (rs[(size_t)i]->as_run.ws) {
       Lo.ws_off[(size_t)i] = off;
-      off += rs[(size_t)i]->ws;
+      off += rs[(size_t)i]->as_run.ws;
     }
   }
   Lo.total = off;
@@ -194,7 +238,7 @@ namespace {
 int occ_key(int fam, int chunk) { return fam * 16 + chunk; }
 
 // Lay out a batch in the slot's staging buffer, copy it to the device arena and
-// launch one persistent kernel per (family, chunk) group, then the fold kernel.
+// launch one kernel per (family, chunk) group, then the fold kernels.
 // These device steps go onto the slot's stream in order.  On failure, *drain says
 // whether some of them were already enqueued: then the slot must stay busy until
 // its stream has finished with the staging buffer and the arena.  The fake executor
@@ -208,7 +252,7 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
   if (Lo.total > slot.cap)
     return fail(HP_ETOOBIG, "batch needs %zu bytes of slot arena, capacity %zu", Lo.total, slot.cap);
   const size_t lds = (size_t)kBatchGroupWaves * kWaveLdsBytes;
-  const int n_steps = 1 + (int)Lo.keys.size() + (Lo.folds.empty() ? 0 : 1);
+  const int n_steps = 1 + (int)Lo.keys.size() + (Lo.folds.empty() ? 0 : 1) + (Lo.n_unit_fold ? 1 : 0);
   // test hook: this batch fails before device step fail_step (0: before the upload)
   int fail_at = -1;
   if (S->fail_every > 0 && slot.batch_id % S->fail_every == 0)
@@ -236,18 +280,41 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
   unsigned char* d = slot.d_arena;
   DevPlan* hp_ = reinterpret_cast<DevPlan*>(h + Lo.plans_off);
   const void** hin = reinterpret_cast<const void**>(h + Lo.ptr_off);
-  void** hout = reinterpret_cast<void**>(h + Lo.ptr_off) + n;
-  unsigned char** hws = reinterpret_cast<unsigned char**>(h + Lo.ptr_off) + 2 * n;
+  void** hout = reinterpret_cast<void**>(h + Lo.ptr_off) + Lo.n_plans;
+  unsigned char** hws = reinterpret_cast<unsigned char**>(h + Lo.ptr_off) + 2 * Lo.n_plans;
+  UnitDesc* hunit = reinterpret_cast<UnitDesc*>(h + Lo.unit_off);
+  int2* hufold = reinterpret_cast<int2*>(h + Lo.unit_fold_off);
   for (int64_t i = 0; i < n; ++i) {
-    hp_[i] = rs[(size_t)i]->L.dp;
-    hin[i] = rs[(size_t)i]->in;
-    hout[i] = rs[(size_t)i]->out;
-    hws[i] = Lo.ws_off[(size_t)i] ? d + Lo.ws_off[(size_t)i] : nullptr;
+    const Request& r = *rs[(size_t)i];
+    const int64_t k = Lo.at[(size_t)i];
+    unsigned char* ws = Lo.ws_off[(size_t)i] ? d + Lo.ws_off[(size_t)i] : nullptr;
+    if (r.unit.on) {
+      UnitDesc D = r.unit.d;
+      D.in = r.in;
+      D.out = r.out;
+      D.ws = ws;
+      hunit[k] = D;
+      for (long long o = 0; o < r.as_run.nfold; ++o) *hufold++ = make_int2((int)k, (int)o);
+      continue;
+    }
+    hp_[k] = r.L.dp;
+    hin[k] = r.in;
+    hout[k] = r.out;
+    hws[k] = ws;
   }
   std::vector<BatchArgs> args(Lo.keys.size());
   std::vector<int> grid(Lo.keys.size());
   for (size_t g = 0; g < Lo.keys.size(); ++g) {
     std::vector<int64_t>& mem = Lo.members[g];
+    if (Lo.keys[g].first >= kUnitFamily) {  // a wave per unit, largest units first
+      std::stable_sort(mem.begin(), mem.end(), [&](int64_t a, int64_t c) {
+        return rs[(size_t)a]->unit.unit_bytes > rs[(size_t)c]->unit.unit_bytes;
+      });
+      int2* t = reinterpret_cast<int2*>(h + Lo.task_off[g]);
+      for (int64_t i : mem)
+        for (int64_t u = 0; u < rs[(size_t)i]->unit.units; ++u) *t++ = make_int2((int)Lo.at[(size_t)i], (int)u);
+      continue;
+    }
     std::stable_sort(mem.begin(), mem.end(), [&](int64_t a, int64_t c) {
       const double wa = (double)rs[(size_t)a]->L.info.in_bytes / (double)rs[(size_t)a]->L.dp.grid;
       const double wc = (double)rs[(size_t)c]->L.info.in_bytes / (double)rs[(size_t)c]->L.dp.grid;
@@ -260,7 +327,7 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
       const double wt = task_cost((double)rs[(size_t)i]->L.info.in_bytes / (double)rs[(size_t)i]->L.dp.grid);
       for (long long w = 0; w < rs[(size_t)i]->L.dp.grid; ++w) {
         weight[(size_t)k] = wt;
-        ordered[(size_t)k++] = make_int2((int)i, (int)w);
+        ordered[(size_t)k++] = make_int2((int)Lo.at[(size_t)i], (int)w);
       }
     }
     const int key = occ_key(Lo.keys[g].first, Lo.keys[g].second);
@@ -292,13 +359,22 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
   // after the first enqueued step, any failure leaves work on the stream
   for (size_t g = 0; g < Lo.keys.size(); ++g, ++step) {
     if ((s = hook(step)) != HP_OK) return s;
+    if (Lo.keys[g].first >= kUnitFamily) {
+      s = launch_units(Lo.keys[g].first - kUnitFamily, reinterpret_cast<const UnitDesc*>(d + Lo.unit_off),
+                       reinterpret_cast<const int2*>(d + Lo.task_off[g]), (int)Lo.ntask[g], slot.st);
+      if (s != HP_OK) {
+        *drain = true;
+        return s;
+      }
+      continue;
+    }
     BatchArgs A = args[g];
     A.plans = reinterpret_cast<const DevPlan*>(d + Lo.plans_off);
     A.tasks = reinterpret_cast<const int2*>(d + Lo.task_off[g]);
     A.ctr = reinterpret_cast<unsigned int*>(d + Lo.ctr_off[g]);
     A.ins = reinterpret_cast<const void* const*>(d + Lo.ptr_off);
-    A.outs = reinterpret_cast<void* const*>(d + Lo.ptr_off) + n;
-    A.wss = reinterpret_cast<unsigned char* const*>(d + Lo.ptr_off) + 2 * n;
+    A.outs = reinterpret_cast<void* const*>(d + Lo.ptr_off) + Lo.n_plans;
+    A.wss = reinterpret_cast<unsigned char* const*>(d + Lo.ptr_off) + 2 * Lo.n_plans;
     s = launch_batch(Lo.keys[g].first, Lo.keys[g].second, A, grid[g], kBatchGroupWaves, lds, slot.st);
     if (s != HP_OK) {
       *drain = true;
@@ -309,8 +385,18 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
     if ((s = hook(step)) != HP_OK) return s;
     s = launch_fold(reinterpret_cast<const DevPlan*>(d + Lo.plans_off),
                     reinterpret_cast<const FoldTask*>(d + Lo.fold_off), (int)Lo.folds.size(),
-                    reinterpret_cast<void* const*>(d + Lo.ptr_off) + n,
-                    reinterpret_cast<unsigned char* const*>(d + Lo.ptr_off) + 2 * n, slot.st);
+                    reinterpret_cast<void* const*>(d + Lo.ptr_off) + Lo.n_plans,
+                    reinterpret_cast<unsigned char* const*>(d + Lo.ptr_off) + 2 * Lo.n_plans, slot.st);
+    if (s != HP_OK) {
+      *drain = true;
+      return s;
+    }
+    ++step;
+  }
+  if (Lo.n_unit_fold) {
+    if ((s = hook(step)) != HP_OK) return s;
+    s = launch_unit_folds(reinterpret_cast<const UnitDesc*>(d + Lo.unit_off),
+                          reinterpret_cast<const int2*>(d + Lo.unit_fold_off), (int)Lo.n_unit_fold, slot.st);
     if (s != HP_OK) {
       *drain = true;
       return s;
@@ -498,7 +584,8 @@ extern "C" hp_status hp_server_create(const hp_server_cfg* cfg, hp_server_t* out
         int o = batch_occupancy(fam, chunk, kBatchGroupWaves, lds);
         S->occ[occ_key(fam, chunk)] = o < 1 ? 1 : o;
       }
-    if (warm_batch_kernels(S->slots[0].st) != HP_OK || hipStreamSynchronize(S->slots[0].st) != hipSuccess) {
+    if (warm_batch_kernels(S->slots[0].st) != HP_OK || warm_unit_kernels(S->slots[0].st) != HP_OK ||
+        hipStreamSynchronize(S->slots[0].st) != hipSuccess) {
       for (Slot& q : S->slots) {
         (void)hipStreamDestroy(q.st);
         (void)hipEventDestroy(q.ev);
@@ -529,23 +616,32 @@ extern "C" hp_status hp_submit(hp_server_t S, const hp_nest* nest, const void* d
   if (S->stop.load()) return fail(HP_ESTATE, "server is shutting down");
   Request r;
   memset(&r.info, 0, sizeof r.info);
-  hp_status s = plan_for_batch(nest, (uint32_t)(S->cfg.flags & HP_FLAG_OUT_F32), true,
-                               kBatchWaves, &r.L);
+  const uint32_t pflags = (uint32_t)(S->cfg.flags & HP_FLAG_OUT_F32);
+  bool tuned = false;
+  hp_status s = plan_for_batch(nest, pflags, true, kBatchWaves, &r.L, &tuned);
   if (s != HP_OK) return s;
   const uintptr_t al = (r.L.info.out_dtype == HP_I64 || r.L.info.out_dtype == HP_F64) ? 7u : 3u;
   if (reinterpret_cast<uintptr_t>(d_out) & al) return fail(HP_EINVAL, "output misaligned");
   r.bytes = r.L.info.in_bytes + r.L.info.out_bytes + r.L.info.workspace_bytes;
   if (r.bytes > S->cfg.hbm_budget)
     return fail(HP_ETOOBIG, "request needs %zu bytes, budget is %zu", r.bytes, (size_t)S->cfg.hbm_budget);
-  r.key = std::make_pair(family_of(r.L.dp), (int)r.L.dp.chunk);
-  r.ntask = r.L.dp.grid;
-  r.nfold = fold_task_count(r.L.dp);
-  r.ws = align_up(r.L.info.workspace_bytes, 256);
-  {
-    const size_t arena = Tally().total_with(r);
-    if (arena > S->cfg.slot_bytes)
-      return fail(HP_ETOOBIG, "request needs %zu bytes of slot arena, slot_bytes is %zu", arena,
-                  (size_t)S->cfg.slot_bytes);
+  r.as_plan = Share{std::make_pair(family_of(r.L.dp), (int)r.L.dp.chunk), (long long)r.L.dp.grid,
+                    (long long)fold_task_count(r.L.dp), A256(r.L.info.workspace_bytes)};
+  const size_t arena = Sum().total_with(r.as_plan);
+  if (arena > S->cfg.slot_bytes)
+    return fail(HP_ETOOBIG, "request needs %zu bytes of slot arena, slot_bytes is %zu", arena,
+                (size_t)S->cfg.slot_bytes);
+  // unit tasks where their share fits a slot too (the request and the server decide it,
+  // never the batch: the same bits whatever it is batched with)
+  r.unit = unit_route(nest, pflags, r.L, tuned);
+  r.as_run = r.as_plan;
+  if (r.unit.on) {
+    r.as_run = Share{std::make_pair(kUnitFamily + r.unit.dtype, 0), (long long)r.unit.units, (long long)r.unit.folds,
+                     A256((size_t)r.unit.ws_bytes)};
+    if (Sum().total_with(r.as_run) > S->cfg.slot_bytes) {
+      r.unit.on = 0;
+      r.as_run = r.as_plan;
+    }
   }
   r.nest = *nest;
   r.in = d_in;

@@ -19,7 +19,7 @@ enum UnitOut : int32_t { UNIT_F64 = 0, UNIT_F32, UNIT_I64, UNIT_I32 };
 //   elements [part_len part, ...) of row u / lparts             (part = u % lparts).
 // With `partial` a unit leaves carriers of M (or, split rows, of L) in ws and a fold task
 // per output ends the nest.
-struct alignas(128) UnitDesc {
+struct UnitDesc {
   const void* in;
   void* out;
   unsigned char* ws;
@@ -36,6 +36,7 @@ struct alignas(128) UnitDesc {
   int32_t out_kind;   // UnitOut
   int32_t partial;
   int32_t direct;     // one segment: a row's value is an output
+  int32_t pad[6];
 };
 static_assert(sizeof(UnitDesc) == 128, "one descriptor is one 128-byte line");
 

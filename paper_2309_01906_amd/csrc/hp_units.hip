@@ -559,6 +559,15 @@ hp_status launch_units_of(int dtype, const UnitDesc* desc, int n, hipStream_t st
   return launched();
 }
 
+hp_status warm_unit_kernels(hipStream_t st) {
+  const dim3 one(1), wg(256);
+  hipLaunchKernelGGL(k_units<float>, one, wg, 0, st, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(k_units<uint16_t>, one, wg, 0, st, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(k_units<int32_t>, one, wg, 0, st, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(k_unit_folds, one, wg, 0, st, nullptr, nullptr, 0);
+  return launched();
+}
+
 hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n, hipStream_t st) {
   if (n <= 0) return HP_OK;
   hipLaunchKernelGGL(k_unit_folds, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, descs, tasks, n);

@@ -11,6 +11,8 @@ namespace hp {
 hp_status launch_units(int dtype, const UnitDesc* descs, const int2* tasks, int n, hipStream_t st);
 // All units of one nest (n of them), in order: the baseline of one launch per nest.
 hp_status launch_units_of(int dtype, const UnitDesc* desc, int n, hipStream_t st);
+// Load the unit kernels: each launched with no tasks.
+hp_status warm_unit_kernels(hipStream_t st);
 // The nests' partial carriers: n fold tasks (nest, output), a wave each.
 hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n, hipStream_t st);
 

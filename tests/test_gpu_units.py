@@ -114,3 +114,42 @@ def test_extremes_and_non_finite_values():
         v[0, v.shape[1] // 2] = bad
     for e, v, got in zip(exts, x, run([(e, ("NONE", "SUM"), hp.F32) for e in exts], x)):
         assert np.isnan(got[0]) and np.isfinite(got[1:]).all(), e
+
+
+@pytest.mark.parametrize("slot_bytes", [8 << 10, 64 << 10, 64 << 20])
+def test_served_units_and_plan_tasks(slot_bytes):
+    """Requests on unit tasks and on plan tasks (four reducing segments), with folds of
+    both kinds, in one server: the same bits as a batch of them where the slot lets the
+    request run alike, and the oracle's values in slots too small for some unit tasks."""
+    shapes = [(e, ("NONE", "SUM"), hp.F32) for e in [(5, 3), (67, 33), (2, 9000), (1, 1000003)]]
+    shapes += [(e, o, hp.I32) for e, o in [((40, 50, 3, 30), ("NONE", "ARGMAX", "SUM", "MIN")), ((2, 3, 70001), ("NONE", "ARGMAX", "SUM")),
+                                          ((300, 77), ("NONE", "ARGMIN")), ((2, 3, 4, 5, 6), ("NONE", "SUM", "MAX", "SUM", "MIN")),
+                                          ((1, 3, 4, 5, 6000), ("NONE", "SUM", "MAX", "SUM", "MIN")), ((9,), ("NONE",))]]
+    hosts = [workloads.normal_f32(950 + i, e) if d == hp.F32 else workloads.uniform_i32(950 + i, e, -9, 9)
+             for i, (e, _, d) in enumerate(shapes)]
+    want = run(shapes, hosts)
+    devs = [to_device(h) for h in hosts]
+    say("case served units", slot_bytes)
+    with hp.Server(slot_bytes=slot_bytes, streams=2, max_batch=32, window_us=200) as s:
+        for _ in range(3):
+            tickets, outs = [], []
+            for k in range(4 * len(shapes)):
+                i = k % len(shapes)
+                e, o, d = shapes[i]
+                outs.append(torch.full(want[i].shape, 77, dtype=torch.from_numpy(want[i]).dtype, device="cuda"))
+                torch.cuda.synchronize()
+                try:
+                    tickets.append(s.submit(e, o, d, devs[i].data_ptr(), outs[-1].data_ptr()))
+                except hp.HPError as err:
+                    assert err.status_name == "HP_ETOOBIG" and slot_bytes == 8 << 10
+                    tickets.append(None)
+            for k, t in enumerate(tickets):
+                if t is None:
+                    continue
+                assert s.wait(t)["status"] == 0
+                i = k % len(shapes)
+                e, o, _ = shapes[i]
+                got = outs[k].cpu().numpy()
+                assert_match(got, hosts[i], e, o, rel=1e-13, what=f"served {e} {o}")
+                if slot_bytes == 64 << 20:
+                    np.testing.assert_array_equal(got, want[i])
