@@ -169,7 +169,17 @@ def kernel_name(inf: PlanInfo, ops=None) -> str:
     kernel's first template argument is the innermost operator (from ``ops``)."""
     c = inf.chunk
     if inf.kernel == KERNEL_ORDERED:
-        return "hp::k_ordered<2, 8>" if inf.out_dtype == AFFINE64 else "hp::k_ordered<4, 4>"
+        w, block = WIDTH[inf.out_dtype], inf.in_elems // inf.n_out
+        if inf.nseg == 0:
+            return "hp::k_ordered_copy"
+        if block <= 64:
+            return f"hp::k_ordered_short<{w}"  # and the rows per wave
+        if inf.waves > 4:
+            return f"hp::k_ordered_join<{w}>"
+        n = min(block, 64 * max(inf.strips))  # elements of a wave
+        if w == 2 and n <= 512:
+            return "hp::k_ordered<2, 512, false>"
+        return f"hp::k_ordered<{w}, {2048 if w == 2 and -(-n // 2048) * 38 <= -(-n // 512) * 14 else 512}, true>"
     if inf.kernel == KERNEL_INT_CHAIN:
         return f"hp::k_nest_i32_chain<{OP_TEMPLATE[_op(ops[-1])] if ops else '?'}, {inf.nseg}>"
     if inf.kernel == KERNEL_INT_DEEP:

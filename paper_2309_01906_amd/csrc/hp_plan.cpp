@@ -239,12 +239,11 @@ static void auto_map(const hp_nest* n, int p, int chunk_last, hp_level_map* m, i
 }
 
 // Ordered products (HP_OP_PROD over AFFINE64 / MAT2X2_64 elements).  The reduced
-// block of an output is contiguous; it is cut into gsplit chunks of ord_span
-// elements, one wavefront each.  Lane l of the wave takes the l-th 64th of the
-// chunk, K elements (one 128-byte line) at a time, into a running product; an
-// order-keeping butterfly multiplies the 64 lane products once per chunk.  Chunks
-// are folded in order by a second kernel.
-static constexpr int kOrdWaves = 4;  // waves per workgroup (independent workers)
+// block of an output is contiguous.  It is one wavefront's, or one workgroup's, or it
+// is cut into gsplit chunks of ord_span elements, a wavefront each, whose products are
+// multiplied in order by a second kernel (hp_ordered.hip).
+static constexpr int kOrdWaves = 4;       // waves per workgroup (independent workers)
+static constexpr int kOrdJoinWaves = 16;  // waves of a workgroup that shares a block
 
 static hp_status lower_ordered(const hp_nest* n, const hp_level_map* map_in, uint32_t flags, Lowered* out,
                                int force_nw) {
@@ -266,14 +265,13 @@ static hp_status lower_ordered(const hp_nest* n, const hp_level_map* map_in, uin
     total *= e;
   }
   const int es = n->dtype == HP_AFFINE64 ? 16 : 32;
-  const int K = 128 / es;  // elements per lane run: one 128-byte line (8 affine maps, 4 matrices)
   DevPlan dp;
   memset(&dp, 0, sizeof dp);
   dp.depth = d;
   dp.p = p;
   dp.dtype = n->dtype;
   dp.flags = (int32_t)flags;
-  dp.chunk = K;
+  dp.chunk = 1;  // an element per lane
   dp.nw = kOrdWaves;
   dp.kernel = HP_KERNEL_ORDERED;
   dp.in_elems = total;
@@ -282,26 +280,30 @@ static hp_status lower_ordered(const hp_nest* n, const hp_level_map* map_in, uin
   for (int l = p; l < d; ++l) block *= n->extent[l];
   dp.n_out = n_out;
   dp.ord_block = block;
-  // chunks: enough wave units to fill the chip several times over, each at least
-  // 4 tiles
-  const int64_t tile = (int64_t)kWave * K;
-  int64_t C = 1;
-  if (p < d) {
-    C = cdiv(16384, n_out);
-    const int64_t by_len = cdiv(block, 4 * tile);
-    if (C > by_len) C = by_len;
-    if (C > 4096) C = 4096;
-    if (C < 1) C = 1;
+  // Few blocks of up to 8 elements per thread of a workgroup are one workgroup's each (no
+  // second kernel: 4.4 us for 4,096 maps, 6.4 in chunks), and a block of up to 16 rows of
+  // 64 elements is a wave's.  Longer ones are cut into units of 8 rows, a tile of maps or
+  // two of matrices: waves that come and go keep the chip more evenly busy than waves
+  // that loop (300 x 20,011 maps: 18.4 us, 19.6 in 2048 units, 22.1 in 4096; 4,096 x
+  // 16,384: 157 us, 165 in 4096 units).  At most 2048 units per output, for the second
+  // kernel (4 x 4,000,000: 42.9 us, 47.3 with all 7,813), and 131,072 in all, whose
+  // products take 4 MiB of workspace.
+  const int64_t rows = cdiv(block, kWave);
+  int64_t per = rows, C = 1;
+  if (p < d && rows > 1 && n_out <= 128 && rows <= 8 * kOrdJoinWaves) {
+    dp.nw = kOrdJoinWaves;
+  } else if (p < d && rows > 16 && n_out <= 65536) {
+    const int64_t most = n_out < 64 ? 2048 : 131072 / n_out;
+    per = cdiv(cdiv(rows, most), 8) * 8;
+    C = cdiv(rows, per);
   }
-  int64_t span = cdiv(cdiv(block, C), tile) * tile;
-  if (span < 1) span = 1;
-  C = cdiv(block, span);
+  const int64_t span = per * kWave;
   dp.ord_span = span;
   dp.gsplit = C;
   dp.gmode = C > 1 ? GCOMB_UNIFORM : GCOMB_NONE;
   const int64_t units = n_out * C;
-  int64_t grid = cdiv(units, kOrdWaves);
-  if (grid > 2048) grid = 2048;  // wave workers walk the units grid-stride
+  int64_t grid = dp.nw == kOrdJoinWaves ? n_out : cdiv(units, kOrdWaves);
+  if (grid > (1 << 21)) grid = 1 << 21;  // the waves walk what is left
   dp.grid = grid;
   dp.out_kind = n->dtype;
   hp_plan_info& I = out->info;
@@ -313,17 +315,17 @@ static hp_status lower_ordered(const hp_nest* n, const hp_level_map* map_in, uin
   I.in_elems = total;
   I.in_bytes = (size_t)total * es;
   I.grid = grid;
-  I.waves = kOrdWaves;
-  I.chunk = K;
+  I.waves = dp.nw;
+  I.chunk = dp.chunk;
   I.gsplit = C;
   I.workspace_bytes = C > 1 ? (size_t)n_out * C * es : 0;
-  I.lds_bytes = (size_t)kOrdWaves * 64 * (K * es + 16);  // one staged tile per wave
+  I.lds_bytes = p == d || block <= kWave ? 0 : dp.nw == kOrdJoinWaves ? (size_t)kOrdJoinWaves * es : (size_t)kOrdWaves * 8192;
   for (int l = 0; l < d; ++l) {
     I.scopes[l] = l < p ? HP_SCOPE_G : (l == p ? (HP_SCOPE_G | HP_SCOPE_W | HP_SCOPE_V | HP_SCOPE_L) : HP_SCOPE_L);
     I.units[l][HP_AXIS_G] = l < p ? (uint32_t)n->extent[l] : (l == p ? (uint32_t)C : 1u);
-    I.units[l][HP_AXIS_W] = l == p ? (uint32_t)kOrdWaves : 1u;
+    I.units[l][HP_AXIS_W] = l == p ? (uint32_t)dp.nw : 1u;
     I.units[l][HP_AXIS_V] = l == p ? (uint32_t)kWave : 1u;
-    I.strips[l] = l == p ? cdiv(span, tile) : 1;
+    I.strips[l] = l == p ? (dp.nw == kOrdJoinWaves ? cdiv(rows, kOrdJoinWaves) : per) : 1;
   }
   I.nseg = p < d ? 1 : 0;
   I.kernel = HP_KERNEL_ORDERED;

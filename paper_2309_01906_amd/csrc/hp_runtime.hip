@@ -106,7 +106,7 @@ extern "C" hp_status hp_run(hp_plan_t plan, const void* d_in, void* d_out, void*
   hp_status s;
   if (plan->rows.kind != hp::ROWS_OFF) return hp::launch_rows(plan->rows, d_in, d_out, plan->ws, st);
   if (plan->segs.kind != hp::SEGS_OFF) return hp::launch_segs(plan->segs, d_in, d_out, plan->ws, st);
-  if (plan->dp.kernel == HP_KERNEL_ORDERED) return hp::launch_ordered(plan->dp, plan->d_dp, d_in, d_out, plan->ws, st);
+  if (plan->dp.kernel == HP_KERNEL_ORDERED) return hp::launch_ordered(plan->dp, d_in, d_out, plan->ws, st);
   switch (plan->dp.dtype) {
     case HP_F32: s = hp::launch_nest_f32(plan->dp, plan->d_dp, d_in, d_out, plan->ws, plan->info.lds_bytes, st); break;
     case HP_BF16: s = hp::launch_nest_bf16(plan->dp, plan->d_dp, d_in, d_out, plan->ws, plan->info.lds_bytes, st); break;

@@ -99,6 +99,7 @@ extern "C" hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* m
   FoldTask* dF = reinterpret_cast<FoldTask*>(base + kStaticPlanBytes);
   void* ws = L.info.workspace_bytes ? base + kStaticWsOffset : nullptr;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  if (P.kernel == HP_KERNEL_ORDERED) return launch_ordered(P, d_in, d_out, ws, st);
   const RowRoute rows = row_route(nest, map, flags, L);
   if (rows.kind != ROWS_OFF) return launch_rows(rows, d_in, d_out, ws, st);  // plain arguments: nothing to install
   const SegRoute segs = seg_route(nest, map, flags, L);
@@ -108,7 +109,6 @@ extern "C" hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* m
   hipLaunchKernelGGL(k_static_install, dim3((unsigned)((n_inst + 255) / 256)), dim3(256), 0, st, P, dP, dF,
                      (int)n_fold);
   if (hipGetLastError() != hipSuccess) return fail(HP_EDEVICE, "plan install launch failed");
-  if (P.kernel == HP_KERNEL_ORDERED) return launch_ordered(P, dP, d_in, d_out, ws, st);
   switch (P.dtype) {
     case HP_F32: s = launch_nest_f32(P, dP, d_in, d_out, ws, L.info.lds_bytes, st); break;
     case HP_BF16: s = launch_nest_bf16(P, dP, d_in, d_out, ws, L.info.lds_bytes, st); break;
