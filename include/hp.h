@@ -414,8 +414,11 @@ hp_status hp_server_destroy(hp_server_t s);
  * multiply-add); boundary cells keep their values.  Levels: each workgroup (8
  * threads per tile row) reads a tile_rows x 64 output tile plus a ghost surface T
  * cells wide into LDS once, runs T sweeps there and writes the tile once; each lane
- * updates column strips of 4 cells from registers; the tiles are dealt to the XCDs in bands, so ghost cells
- * that neighbouring tiles share come from HBM once into the XCD's L2.  More sweeps
+ * updates column strips of 4 cells from registers; the tiles are dealt to the XCDs in
+ * bands, so ghost cells that neighbouring tiles share come from HBM once into the XCD's
+ * L2.  Where that is faster, launches of several sweeps stream the rows of 256-column
+ * strips through a wave's registers instead, with the same bits (a chosen tile_rows or
+ * HP_STENCIL_NO_XCD keeps the LDS tiles, and hp_stencil_info names them).  More sweeps
  * than one launch holds (8) run as ceil(steps / T) launches, alternating between
  * d_out and a rows x cols buffer the plan allocates, so that the last writes d_out.
  * hp_stencil_plan: rows, cols >= 1, steps >= 1 (HP_EINVAL); at most 8 sweeps per
