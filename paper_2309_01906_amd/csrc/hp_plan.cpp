@@ -1059,10 +1059,24 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   while (2 * (int64_t)S.eM <= (rows >> S.pair_bits)) ++S.pair_bits;
   const int64_t steps = cdiv(S.eM, rows >> S.pair_bits);
   S.steps = (int32_t)steps;
-  int64_t nw = cdiv(want / 2, pairs);  // waves per pair that fill the chip, each with two steps or more
+  // Waves per pair.  Up to two vectors per lane: enough to fill the chip, each with two
+  // steps or more, and some 4 KiB of input each, all of it in flight: waves
+  // that come and go read memory in order and leave no tail (64 x 128 x 64 x 64, 16 KiB
+  // pairs: 4 waves of a pair 26.9 us, a wave 32.0, 8 waves 45).  Longer rows are 4 KiB a
+  // step already: a few waves that walk a pair are as good (1024 x 64 x 1024: 41.9 us with
+  // 4096 of them, 49 with 8192), but for pairs of four rows (8192 x 4 x 1024: 21.6 us,
+  // 24.5 with a wave each).
+  const int64_t pair_bytes = 4 * (int64_t)S.eL * S.eM;
+  const bool small = S.vecs <= 2;
+  int64_t nw = cdiv(small ? want : want / 2, pairs);
   if (nw > steps / 2) nw = steps / 2;
+  const int64_t filled = cdiv(pair_bytes, pairs < 1024 ? 2048 : 4096);
+  if (small && nw > filled) nw = filled;
+  if (small && nw < 8 && steps >= 8 && pair_bytes >= 3 * 4096) nw = pair_bytes < 8 * 4096 ? 4 : 8;
+  if (!small && steps == 4) nw = 4;
   S.waves = nw > 4 ? 8 : nw > 1 ? 4 : 1;
   int64_t parts = nw / 8 < 1 ? 1 : nw / 8;
+  if (parts > 1 && small && parts > cdiv(pair_bytes, 8 * 4096)) parts = cdiv(pair_bytes, 8 * 4096);
   const int64_t per = cdiv(steps, parts);
   parts = cdiv(steps, per);
   S.per = (int32_t)per;
@@ -1071,11 +1085,28 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   S.units = (uint32_t)(pairs * parts);
   if (S.waves == 1) {
     const int64_t groups = cdiv(pairs, (int64_t)1 << S.pair_bits);
-    S.run = (int32_t)cdiv(groups, want);
+    // As many groups as make 4 KiB, or 8 where steps are short and cost their arithmetic
+    // (65536 x 33 x 17, 544 bytes a step: runs of 1, 3 and 6 pairs take 43, 29.5 and 29.1
+    // us; 65536 x 2 x 256, 1 KiB a step: of 2, 4 and 8 pairs 21.7, 24.3 and 28 us), in
+    // whole rounds of steps (300000 x 2 x 4 x 5: runs of 8, 9 and 16 take 27.7, 32.8 and
+    // 28.1 us), while that leaves 4096 waves.
+    int64_t run = cdiv(groups, want);
+    if (small) {
+      const int64_t group_bytes = pair_bytes << S.pair_bits, aim = group_bytes < 768 * steps ? 8192 : 4096;
+      const int64_t round = S.vecs == 2 ? 2 : 4, whole = steps % round == 0 ? 1 : steps % 2 == 0 ? round / 2 : round;
+      const int64_t most = groups / (want / 2) < 1 ? 1 : groups / (want / 2);
+      run = (aim + group_bytes / 2) / group_bytes;
+      if (run > most) run = most;
+      if (run >= whole) run = run / whole * whole;
+      if (run < 1) run = 1;
+    }
+    if (run * (S.eL * S.eM << S.pair_bits) > ((int64_t)1 << 28)) run = 1;  // a run's bytes below 2^31
+    S.run = (int32_t)run;
     S.grid = (uint32_t)cdiv(cdiv(groups, S.run), 4);
   }
   S.tail = (ns == 3 || parts > 1) ? 1 : 0;
-  if (S.tail && parts == 1 && (int64_t)S.eM * S.eL < 8) return off;  // the carriers would outweigh the input
+  // carriers that outweigh the input, unless they are few
+  if (S.tail && parts == 1 && (int64_t)S.eM * S.eL < 8 && pairs > (1 << 18)) return off;
   S.ws_bytes = S.tail ? (uint64_t)S.units * kSlotBytes : 0;
   S.kind = SEGS_SHORT;
   return S;

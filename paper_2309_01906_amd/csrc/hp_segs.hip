@@ -7,10 +7,17 @@
 //     wave takes 64 / 2^lb rows a step, 2^lb lanes each; a row's value goes into its
 //     lane group's carrier of M, and the groups, the waves and (in the tail) the parts
 //     of one (o, q) meet once at the end.
+//     With as many pairs as fill the chip a wave runs through one or several (k_seg_run),
+//     some of them side by side when M is short.
 //   longer rows: the row kernels reduce every row to one value first.
-//     With as many pairs as fill the chip a wave runs through several (k_seg_run), some
-//     of them side by side when M is short.
 // k_seg_tail then reduces what is left: the parts of M, or its values, and Q.
+//
+// Measured, from 4096 to 8192 waves that walk their pairs to waves of some 4 KiB:
+//   64 x 128 x 64 x 64 SUM, MAX, ARGMIN (128 MiB)      32.0 -> 26.8 us
+//   61 x 125 x 67 x 59 SUM, MAX, ARGMIN                31.4 -> 27.8 us
+//   65536 x 33 x 17 SUM, MAX (147 MB)                  37.2 -> 27.7 us
+//   20000 x 30 x 200 SUM, MAX (480 MB)                 85.8 -> 67.9 us
+//   30000 x 7 x 30 ARGMIN, SUM (25 MB; keys instead of (value, index) pairs)  19.7 -> 11.9 us
 #include "hp_segs.h"
 
 #include "hp_fold.h"
@@ -44,18 +51,31 @@ __device__ __forceinline__ void outer_add(IAcc& a, long long x, int t, int op, b
 
 __device__ __forceinline__ IAcc iacc_shfl(IAcc a, int b, int lane) { return IntT::shfl(a, 1 << b, lane); }
 
-// The carrier of M: one 64-bit key (IntK) while an ARG level's children fit 32 bits,
-// else (an ARG of int64 sums) a (value, index) pair.  Children of one lane come with
-// growing m.
+// The carrier of M: a sum, or one 64-bit key of which the least or the greatest counts.
+// An ARG level's key is value << shift | index (complemented for ARGMAX, so that the
+// lower index wins), the shift 32 for 32-bit children and the bits of an index for int64
+// sums, which leave it room: a row and M together have at most 2^28 elements.
 struct KeyM {
   typedef long long Acc;
-  __device__ static __forceinline__ Acc identity(int op) { return IntK::identity(op); }
-  __device__ static __forceinline__ void add(Acc& a, long long x, int m, int op, bool ok) {
-    const long long k = IntK::key(x, m, op);
-    a = IntK::merge(a, ok ? k : IntK::identity(op), op);
+  int op, shift;
+  long long mask;
+  bool arg, minlike;
+  __device__ __forceinline__ KeyM(const SegRoute& S, bool wide)
+      : op(S.opM), shift(wide ? 32 - __builtin_clz((unsigned)S.eM) : 32), mask((1ll << shift) - 1), arg(IntK::arg(S.opM)),
+        minlike(IntK::minlike(S.opM)) {}
+  __device__ __forceinline__ Acc identity() const { return IntK::identity(op); }
+  __device__ __forceinline__ void add(Acc& a, long long x, int m, bool ok) const {
+    if (op == HP_OP_SUM) {
+      a = (long long)((unsigned long long)a + (unsigned long long)(ok ? x : 0));
+      return;
+    }
+    long long k = x;
+    if (arg) k = (long long)((unsigned long long)x << shift) | (minlike ? (long long)m : mask ^ m);
+    if (minlike) a = ok && k < a ? k : a;
+    else a = ok && k > a ? k : a;
   }
   // over the lane groups: bits lo .. hi - 1, the bits below lo hold one value
-  __device__ static __forceinline__ Acc lanes(Acc a, int lo, int hi, int lane, int op) {
+  __device__ __forceinline__ Acc lanes(Acc a, int lo, int hi, int lane) const {
     const uint32_t vm = (1u << hi) - (1u << lo);
     if (!vm) return a;
     if (op == HP_OP_SUM) {
@@ -67,24 +87,25 @@ struct KeyM {
       if (vm & 32u) a = key_sum_step<5>(a, true, lane);
       return a;
     }
-    if (IntK::minlike(op)) return key_minmax<true>(a, vm, vm, lane);
+    if (minlike) return key_minmax<true>(a, vm, vm, lane);
     return key_minmax<false>(a, vm, vm, lane);
   }
-  __device__ static __forceinline__ IAcc pair(Acc a, int op) {
-    if (!IntK::arg(op)) return IAcc{a, 0, 0};
-    return IAcc{(long long)(int)(uint32_t)((unsigned long long)a >> 32), (int)IntK::emit(a, op), 0};
+  __device__ __forceinline__ IAcc pair(Acc a) const {
+    if (!arg) return IAcc{a, 0, 0};
+    return IAcc{a >> shift, (int)((minlike ? a : ~a) & mask), 0};
   }
 };
-struct PairM {
-  typedef IAcc Acc;
-  __device__ static __forceinline__ Acc identity(int op) { return IntT::identity(op); }
-  __device__ static __forceinline__ void add(Acc& a, long long x, int m, int op, bool ok) { outer_add(a, x, m, op, ok); }
-  __device__ static __forceinline__ Acc lanes(Acc a, int lo, int hi, int lane, int op) {
-    for (int b = lo; b < hi; ++b) a = IntT::merge(a, iacc_shfl(a, b, lane), op);
-    return a;
-  }
-  __device__ static __forceinline__ IAcc pair(Acc a, int) { return a; }
-};
+
+// Rows are read through a buffer descriptor, so that a step that does not exist -- past
+// the end of a pair, where a wave has fewer steps than loads -- costs no memory traffic:
+// its offset lies beyond the buffer, and the load returns zeros.  (Repeating the last row
+// instead is no cheaper than reading another one: 16 steps on waves that load 4 at a time,
+// 2 of them repeats, took 48.9 us, without repeats 26.4.)
+constexpr uint32_t kNoRow = 0x80000000u;  // pairs and runs hold fewer bytes
+constexpr int kNt = 2;                    // nontemporal
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const int32_t* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(base), 0, (int)bytes, 0x00027000);  // raw dwords
+}
 
 // One row on 2^lb lanes: where this lane's vectors lie, and which of their elements
 // count (an element that the vector before already has does not; ARG indices follow).
@@ -106,16 +127,19 @@ struct SegRow {
       keep[k] = keep_from<int32_t>(t - at[k]);
     }
   }
-  __device__ __forceinline__ void load(const int32_t* base, uint32_t off, i32x4* x) const {
-    typedef const __attribute__((address_space(1))) Vec<int32_t>::E GV;
-    if constexpr (K < 0) {
-      typedef int E __attribute__((ext_vector_type(-K), aligned(4)));
-      const E v = __builtin_nontemporal_load((const __attribute__((address_space(1))) E*)(base + off));
-#pragma unroll
-      for (int e = 0; e < -K; ++e) x[0][e] = v[e];
+  // The row at byte `off` of a buffer; kNoRow loads nothing.
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t buf, uint32_t off, i32x4* x) const {
+    if constexpr (K == -1) {
+      x[0].x = (int)__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, kNt);
+    } else if constexpr (K == -2) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b64(buf, off, 0, kNt);
+      x[0].x = (int)v[0], x[0].y = (int)v[1];
+    } else if constexpr (K == -3) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b96(buf, off, 0, kNt);
+      x[0].x = (int)v[0], x[0].y = (int)v[1], x[0].z = (int)v[2];
     } else {
 #pragma unroll
-      for (int k = 0; k < KK; ++k) x[k] = __builtin_nontemporal_load((GV*)(base + (off + (uint32_t)at[k])));
+      for (int k = 0; k < KK; ++k) x[k] = (i32x4)__builtin_amdgcn_raw_buffer_load_b128(buf, off + 4u * (uint32_t)at[k], 0, kNt);
     }
   }
   // the row's value, on every lane of its group
@@ -144,12 +168,33 @@ __device__ __forceinline__ void seg_out(const SegRoute& S, void* out, IAcc* ws, 
   }
 }
 
+// Steps u = 0 .. U - 1 of a round, kTogether at a time (their chains overlap); `next`
+// loads the step U later into the freed registers (kMore: there is another round).
+constexpr int kTogether = 4;
+template <int OP, int K, int U, bool kMore, class Row, class Next, class Done>
+__device__ __forceinline__ void seg_round(const Row& row, i32x4 (&x)[U][SegRow<OP, K>::KK], int lane, int count, Next next,
+                                          Done done) {
+  constexpr int N = U < kTogether ? U : kTogether;
+#pragma unroll
+  for (int u = 0; u < U; u += N) {
+    if (kMore || u == 0 || u < count) {
+      long long v[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        v[j] = row.reduce(x[u + j], lane);
+        if constexpr (kMore) next(x[u + j]);
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j) done(v[j], u + j);
+    }
+  }
+}
+
 // One (o, q) pair and part per workgroup of NW waves.  K vectors per lane and row (-1
 // to -3: rows of that many elements, a lane each), U steps in flight.
-template <int OP, int K, class M, int NW, int U>
+template <int OP, int K, int NW, int U>
 __global__ void __launch_bounds__(NW* kWave)
     k_seg_rows(const int32_t* __restrict__ in, void* __restrict__ out, IAcc* __restrict__ ws, SegRoute S) {
-  typedef Red<int32_t, OP> R;
   const int lane = (int)(threadIdx.x & 63);
   const int w = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t unit = xcd_run(blockIdx.x, gridDim.x);  // pair * parts + part
@@ -157,124 +202,102 @@ __global__ void __launch_bounds__(NW* kWave)
   const int lb = S.lane_bits, eM = S.eM;
   const int g = lane >> lb, rows = 64 >> lb;
   const SegRow<OP, K> row(S, lane);
-  // rows lie within 2^31 bytes of their pair's first (the planner checked): 32-bit offsets
-  const int32_t* base = in + (long long)pair * eM * S.eL;
-  const uint32_t lane_off = (uint32_t)(g * S.eL), last_off = (uint32_t)((eM - 1) * S.eL);
+  const KeyM M(S, OP == HP_OP_SUM);
+  const uint32_t block = (uint32_t)(eM * S.eL);
+  const __amdgpu_buffer_rsrc_t buf = buffer_of(in + (long long)pair * block, 4u * block);
   // this wave's steps: part * per + w, then every NW-th
   const int s1 = ((int)part + 1) * S.per < S.steps ? ((int)part + 1) * S.per : S.steps;
   const int s0 = (int)part * S.per + w;
-  constexpr int KK = SegRow<OP, K>::KK;
-  auto load = [&](int s, i32x4* x) {
-    row.load(base, min((uint32_t)(s * rows * S.eL) + lane_off, last_off), x);
+  const uint32_t step = 4u * (uint32_t)(rows * S.eL), lane_off = 4u * (uint32_t)(g * S.eL);
+  int ls = s0;  // the step that is loaded next
+  auto next = [&](i32x4* x) {
+    row.load(buf, ls < s1 && ls * rows + g < eM ? (uint32_t)ls * step + lane_off : kNoRow, x);
+    ls += NW;
   };
-  typename M::Acc acc = M::identity(S.opM);
-  i32x4 x[U][KK];
+  long long acc = M.identity();
+  i32x4 x[U][SegRow<OP, K>::KK];
 #pragma unroll
-  for (int u = 0; u < U; ++u) load(s0 + u * NW, x[u]);
-  for (int s = s0; s < s1; s += U * NW) {
-    i32x4 y[U][KK];
-    const bool more = s + U * NW < s1;
-    if (more) {
+  for (int u = 0; u < U; ++u) next(x[u]);
+  int s = s0;
+  auto done = [&](long long v, int u) {
+    const int su = s + u * NW, m = su * rows + g;
+    M.add(acc, v, m, m < eM && su < s1);
+  };
+  if constexpr (U == 1) {  // 4 KiB a step: the next one is loaded while this one is reduced, no more
+    for (; s < s1; s += NW) {
+      i32x4 y[SegRow<OP, K>::KK];
+      next(y);
+      done(row.reduce(x[0], lane), 0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) load(s + (U + u) * NW, y[u]);
+      for (int k = 0; k < SegRow<OP, K>::KK; ++k) x[0][k] = y[k];
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int su = s + u * NW, m = su * rows + g;
-      M::add(acc, row.reduce(x[u], lane), m, S.opM, m < eM && su < s1);
-    }
-    if (more) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int k = 0; k < KK; ++k) x[u][k] = y[u][k];
-    }
+  } else {
+    for (; s + U * NW < s1; s += U * NW) seg_round<OP, K, U, true>(row, x, lane, U, next, done);
+    seg_round<OP, K, U, false>(row, x, lane, (s1 - s + NW - 1) / NW, next, done);
   }
   // the wave's lane groups, then its workgroup's waves
-  acc = M::lanes(acc, lb, 6, lane, S.opM);
+  acc = M.lanes(acc, lb, 6, lane);
   __shared__ IAcc slot[NW];
-  if (lane == 0) slot[w] = M::pair(acc, S.opM);
+  if (lane == 0) slot[w] = M.pair(acc);
   __syncthreads();
   if (w != 0 || lane != 0) return;
-  IAcc r = slot[0];
+  IAcc a = slot[0];
 #pragma unroll
-  for (int j = 1; j < NW; ++j) r = IntT::merge(r, slot[j], S.opM);
-  seg_out(S, out, ws, unit, r);
+  for (int j = 1; j < NW; ++j) a = IntT::merge(a, slot[j], S.opM);
+  seg_out(S, out, ws, unit, a);
 }
 
 // A run of (o, q) pairs per wave.  A step is 64 / 2^lb rows: of 2^pb pairs at once when
 // M has no more rows than that leaves each, else of one pair, whose carrier is complete
 // after S.steps steps.  The loads of U steps are in flight across pairs.
-template <int OP, int K, class M, int U>
+template <int OP, int K, int U>
 __global__ void __launch_bounds__(256)
     k_seg_run(const int32_t* __restrict__ in, void* __restrict__ out, IAcc* __restrict__ ws, SegRoute S) {
   const int lane = (int)(threadIdx.x & 63);
   const int w = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const long long wave = (long long)xcd_run(blockIdx.x, gridDim.x) * 4 + w;
-  const int lb = S.lane_bits, top = 6 - S.pair_bits, eM = S.eM;
+  const int lb = S.lane_bits, pb = S.pair_bits, top = 6 - pb, eM = S.eM;
   const int pr = lane >> top, g = (lane & ((1 << top) - 1)) >> lb, rows = 1 << (top - lb);
   const bool lead = (lane & ((1 << top) - 1)) == 0;
-  const long long pairs = S.n_out * S.eQ, groups = (pairs + (1 << S.pair_bits) - 1) >> S.pair_bits;
+  const long long pairs = S.n_out * S.eQ, groups = (pairs + (1 << pb) - 1) >> pb;
   const long long g0 = wave * S.run, g1 = g0 + S.run < groups ? g0 + S.run : groups;
   if (g0 >= g1) return;
   const SegRow<OP, K> row(S, lane);
-  constexpr int KK = SegRow<OP, K>::KK;
-  long long lg = g0;  // the step whose loads come next
-  int ls = 0;
-  // 32-bit offsets from the group's first element, as above; in the last group the lanes
-  // of pairs that do not exist read its last pair
-  const uint32_t block = (uint32_t)(eM * S.eL), step = (uint32_t)(rows * S.eL);
-  const uint32_t lane_off = (uint32_t)(g * S.eL), last_off = (uint32_t)((eM - 1) * S.eL);
-  const uint32_t here = (uint32_t)pr * block;
-  const uint32_t over = min((uint32_t)pr, (uint32_t)(pairs - 1 - ((groups - 1) << S.pair_bits))) * block;
-  const int32_t* base = in + (lg << S.pair_bits) * block;
-  const long long hop = (long long)block << S.pair_bits;
-  uint32_t off = 0;
-  auto load = [&](i32x4* x) {
-    row.load(base, (lg < groups - 1 ? here : over) + min(off + lane_off, last_off), x);
-    off += step;
+  const KeyM M(S, OP == HP_OP_SUM);
+  // the run's pairs; what lies beyond them is beyond the buffer
+  const uint32_t block = (uint32_t)(eM * S.eL);
+  const long long p0 = g0 << pb, p1 = g1 << pb < pairs ? g1 << pb : pairs;
+  const __amdgpu_buffer_rsrc_t buf = buffer_of(in + p0 * block, 4u * (uint32_t)(p1 - p0) * block);
+  const uint32_t hop = (4u * block) << pb, step = 4u * (uint32_t)(rows * S.eL);
+  uint32_t at = 4u * ((uint32_t)pr * block + (uint32_t)(g * S.eL));  // this lane's row of the step that is loaded next
+  int ls = 0, n = (int)(g1 - g0) * S.steps, left = n;
+  auto next = [&](i32x4* x) {
+    row.load(buf, left > 0 && ls * rows + g < eM ? at : kNoRow, x);
+    --left;
+    at += step;
     if (++ls == S.steps) {
       ls = 0;
-      off = 0;
-      if (lg < groups - 1) {
-        ++lg;
-        base += hop;
-      }
+      at += hop - (uint32_t)S.steps * step;
     }
   };
-  i32x4 x[U][KK];
+  i32x4 x[U][SegRow<OP, K>::KK];
 #pragma unroll
-  for (int u = 0; u < U; ++u) load(x[u]);
-  typename M::Acc acc = M::identity(S.opM);
+  for (int u = 0; u < U; ++u) next(x[u]);
+  long long acc = M.identity(), pair = p0 + pr;
   int cs = 0;
-  long long cg = g0;
-  for (long long left = (g1 - g0) * S.steps; left > 0; left -= U) {
-    i32x4 y[U][KK];
-    const bool more = left > U;
-    if (more) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) load(y[u]);
+  auto done = [&](long long v, int) {
+    const int m = cs * rows + g;
+    M.add(acc, v, m, m < eM);
+    if (++cs == S.steps) {  // the pair is complete: its lane groups meet
+      acc = M.lanes(acc, lb, top, lane);
+      if (lead && pair < p1) seg_out(S, out, ws, pair, M.pair(acc));
+      acc = M.identity();
+      cs = 0;
+      pair += 1ll << pb;
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int m = cs * rows + g;
-      M::add(acc, row.reduce(x[u], lane), m, S.opM, m < eM);
-      if (++cs == S.steps) {  // the pair is complete: its lane groups meet
-        acc = M::lanes(acc, lb, top, lane, S.opM);
-        const long long pair = (cg << S.pair_bits) + pr;
-        if (lead && cg < g1 && pair < pairs) seg_out(S, out, ws, pair, M::pair(acc, S.opM));
-        acc = M::identity(S.opM);
-        cs = 0;
-        ++cg;
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int k = 0; k < KK; ++k) x[u][k] = y[u][k];
-    }
-  }
+  };
+  for (; n > U; n -= U) seg_round<OP, K, U, true>(row, x, lane, U, next, done);
+  seg_round<OP, K, U, false>(row, x, lane, n, next, done);
 }
 
 // Output o on one workgroup: for every q, the eM entries (o, q, m) -- carriers of M
@@ -343,26 +366,28 @@ __global__ void __launch_bounds__(1024) k_seg_tail(const In* __restrict__ ws, vo
   }
 }
 
-template <int OP, int K, class M, int U>
+// Steps in flight: 8 KiB of a wave's input.
+template <int OP, int K>
 void rows_nw(const SegRoute& S, const int32_t* in, void* out, IAcc* ws, hipStream_t st) {
+  constexpr int U = K < 0 ? 8 : K == 1 ? 4 : 2, UR = K <= 2 ? U : 1;
   if (S.waves == 1)
-    hipLaunchKernelGGL((k_seg_run<OP, K, M, U>), dim3(S.grid), dim3(256), 0, st, in, out, ws, S);
+    hipLaunchKernelGGL((k_seg_run<OP, K, U>), dim3(S.grid), dim3(256), 0, st, in, out, ws, S);
   else if (S.waves == 4)
-    hipLaunchKernelGGL((k_seg_rows<OP, K, M, 4, U>), dim3(S.units), dim3(256), 0, st, in, out, ws, S);
+    hipLaunchKernelGGL((k_seg_rows<OP, K, 4, UR>), dim3(S.units), dim3(256), 0, st, in, out, ws, S);
   else
-    hipLaunchKernelGGL((k_seg_rows<OP, K, M, 8, U>), dim3(S.units), dim3(512), 0, st, in, out, ws, S);
+    hipLaunchKernelGGL((k_seg_rows<OP, K, 8, UR>), dim3(S.units), dim3(512), 0, st, in, out, ws, S);
 }
 
-template <int OP, class M>
+template <int OP>
 void rows_op(const SegRoute& S, const int32_t* in, void* out, IAcc* ws, hipStream_t st) {
   switch (S.vecs) {
-    case -1: rows_nw<OP, -1, M, 8>(S, in, out, ws, st); break;
-    case -2: rows_nw<OP, -2, M, 8>(S, in, out, ws, st); break;
-    case -3: rows_nw<OP, -3, M, 8>(S, in, out, ws, st); break;
-    case 1: rows_nw<OP, 1, M, 4>(S, in, out, ws, st); break;
-    case 2: rows_nw<OP, 2, M, 2>(S, in, out, ws, st); break;
-    case 3: rows_nw<OP, 3, M, 1>(S, in, out, ws, st); break;
-    default: rows_nw<OP, 4, M, 1>(S, in, out, ws, st); break;
+    case -1: rows_nw<OP, -1>(S, in, out, ws, st); break;
+    case -2: rows_nw<OP, -2>(S, in, out, ws, st); break;
+    case -3: rows_nw<OP, -3>(S, in, out, ws, st); break;
+    case 1: rows_nw<OP, 1>(S, in, out, ws, st); break;
+    case 2: rows_nw<OP, 2>(S, in, out, ws, st); break;
+    case 3: rows_nw<OP, 3>(S, in, out, ws, st); break;
+    default: rows_nw<OP, 4>(S, in, out, ws, st); break;
   }
 }
 
@@ -413,14 +438,11 @@ hp_status launch_segs(const SegRoute& S, const void* in, void* out, void* ws, hi
   } else {
     IAcc* w = reinterpret_cast<IAcc*>(ws);
     switch (S.opL) {
-      case HP_OP_MIN: rows_op<HP_OP_MIN, KeyM>(S, x, out, w, st); break;
-      case HP_OP_MAX: rows_op<HP_OP_MAX, KeyM>(S, x, out, w, st); break;
-      case HP_OP_ARGMIN: rows_op<HP_OP_ARGMIN, KeyM>(S, x, out, w, st); break;
-      case HP_OP_ARGMAX: rows_op<HP_OP_ARGMAX, KeyM>(S, x, out, w, st); break;
-      default:
-        if (S.opM == HP_OP_ARGMIN || S.opM == HP_OP_ARGMAX) rows_op<HP_OP_SUM, PairM>(S, x, out, w, st);
-        else rows_op<HP_OP_SUM, KeyM>(S, x, out, w, st);
-        break;
+      case HP_OP_MIN: rows_op<HP_OP_MIN>(S, x, out, w, st); break;
+      case HP_OP_MAX: rows_op<HP_OP_MAX>(S, x, out, w, st); break;
+      case HP_OP_ARGMIN: rows_op<HP_OP_ARGMIN>(S, x, out, w, st); break;
+      case HP_OP_ARGMAX: rows_op<HP_OP_ARGMAX>(S, x, out, w, st); break;
+      default: rows_op<HP_OP_SUM>(S, x, out, w, st); break;
     }
     if (S.tail) tail<IAcc, true>(S, (int)S.parts, w, out, st);
   }

@@ -87,3 +87,26 @@ def test_static_entry_and_graph_replay():
                 p.run(x, a)
                 torch.cuda.synchronize()
                 assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("ops", [("MAX", "ARGMIN"), ("ARGMIN", "SUM"), ("SUM", "MAX", "SUM"), ("ARGMAX", "SUM", "MIN")])
+def test_waves_per_pair_and_runs_at_their_edges(ops):
+    """Pairs around the sizes where a wave's run, four or eight waves of a pair and parts
+    take over, with steps that do not fill the last round."""
+    q = (3,) if len(ops) == 3 else ()
+    for ext in [(700, 48, 64), (700, 47, 65), (700, 49, 63), (200, 127, 64), (200, 129, 64), (90, 260, 128), (2, 3000, 67),
+                (5000, 5, 17), (9001, 9, 13), (20011, 2, 5), (12289, 1, 9), (4097, 4, 1024), (4099, 4, 1021), (30, 70, 300),
+                (8200, 33, 2), (600, 500, 3), (5, 20000, 1), (40, 3, 3)]:
+        check(ext[:1] + q + ext[1:], ("NONE",) + ops, -4, 4, 350)
+
+
+def test_arg_of_extreme_sums():
+    """Keys of an ARG level over int64 sums at the ends of their range, with ties."""
+    lo, hi = np.iinfo(np.int32).min, np.iinfo(np.int32).max
+    for ext in [(4, 7, 3), (4, 5, 1000), (3, 3000, 64), (2, 1, 33), (2, 64, 1), (2, 65, 4)]:
+        for fill, other in [(lo, hi), (hi, lo), (lo, lo), (hi, hi)]:
+            x = np.full(ext, fill, np.int32)
+            x[1:, ext[1] // 2, ext[2] // 2:] = other
+            for op in ["ARGMIN", "ARGMAX"]:
+                got, _ = gpu_reduce(x, ext, ("NONE", op, "SUM"))
+                assert_match(got, x, ext, ("NONE", op, "SUM"), what=f"sums {ext} {op}")
