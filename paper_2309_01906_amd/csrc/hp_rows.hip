@@ -12,6 +12,12 @@
 // Short blocks start at any element, so their vectors are loaded at the element type's
 // alignment (global memory takes any); the last vector of a block is moved back to end
 // with it.  MIN, MAX and ARG may see an element twice; sums drop the repeated ones.
+//
+// Measured, short blocks, from 8192 waves that walk the rows to a round of steps per wave
+// and 16 or 32 lanes with up to three vectors each:
+//   float 100000 x 600 (240 MB)    41.9 -> 34.2 us     bf16 100000 x 1000 (200 MB)  34.7 -> 29.6 us
+//   float 300000 x 130             42.5 -> 26.2 us     bf16 500000 x 130            38.2 -> 30.4 us
+//   int32 100003 x 129 ARGMIN      16.2 -> 10.4 us     float 2000000 x 16           26.9 -> 23.3 us
 #include "hp_rows.h"
 
 #include "hp_fold.h"
