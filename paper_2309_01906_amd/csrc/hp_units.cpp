@@ -12,10 +12,12 @@ static inline int log2u(uint64_t x) {
   return r;
 }
 
-// The cost of one unit, in vectors per lane (1 KiB of input each).  A wave keeps 8 of
-// them in flight, so 24 take it some 6 us under load: a fraction of a batch's time, and
-// enough to pay for a unit's start.  The end of a step of rows costs as much as a few
-// vectors (its butterfly, and the carrier of M): short rows make smaller units.
+// The cost of one unit, in vectors per lane (1 KiB of input each).  A wave pays some 2 us
+// for its task and its descriptor before its first data, so smaller units cost more than
+// the finer tail gains, and larger ones leave a few waves behind in small batches (10,000
+// bf16 nests / 300 mixed ones: cost 8 111 / 51 us, 16 89 / 39, 24 82.5 / 38, 40 84 / 46).
+// The end of a step of rows costs as much as a few vectors (its butterfly, and the
+// carrier of M): short rows make smaller units.
 static constexpr int64_t kUnitCost = 24;
 
 UnitRoute unit_route(const hp_nest* n, uint32_t flags, const Lowered& L, bool tuned) {

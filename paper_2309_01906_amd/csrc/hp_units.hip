@@ -289,9 +289,10 @@ __device__ __forceinline__ void unit_task(const UnitDesc& D, uint32_t unit, int 
       const V xl = vector(row, at);
       Acc a = R.identity();
       if (full > 0) {
-        // no load sits in a branch (the compiler would wait for all of them): a batch
-        // that runs past the row's end repeats its last whole pass
-        auto pass_t = [&](int i) { return (uint32_t)(min(i, full - 1) * 64 * N + lane * N); };
+        // no load sits in a branch (the compiler would wait for all of them): the passes
+        // of a batch past the row's end read its first vector, all lanes the same one
+        // (repeating the last pass costs as much traffic as another one)
+        auto pass_t = [&](int i) { return i < full ? (uint32_t)(i * 64 * N + lane * N) : 0u; };
         V x[kLong];
 #pragma unroll
         for (int u = 0; u < kLong; ++u) x[u] = vector(row, pass_t(u));
@@ -320,22 +321,26 @@ __device__ __forceinline__ void unit_task(const UnitDesc& D, uint32_t unit, int 
   }
   // Short rows, kRows steps together.  Element offsets from the unit's first element in
   // 32 bits (the partition keeps a unit below 2^28 elements); a group's pairs that do not
-  // exist read its first pair, rows beyond M its last, steps beyond the unit its last group.
+  // exist read its first pair, rows beyond M its last, and the steps beyond the unit its
+  // first vector, all lanes the same one.
   const uint32_t lane_off = (uint32_t)(g * eL), last_off = (uint32_t)((eM - 1) * eL), row_step = (uint32_t)(rows * eL);
   const Raw* base = in + (g0 << pb) * block;
   const uint32_t hop = (uint32_t)block << pb;
   const int n_groups = (int)(g1 - g0);
   int lg = 0, ls = s0;  // the step whose offset comes next
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
   auto next_row = [&]() -> uint32_t {
+    if (lg >= n_groups) return kNone;
     const uint32_t po = ((g0 + lg) << pb) + pr < pairs ? (uint32_t)pr * (uint32_t)block : 0u;
     const uint32_t ro = (uint32_t)lg * hop + po + min((uint32_t)ls * row_step + lane_off, last_off);
     if (++ls == s1) {
       ls = s0;
-      if (lg + 1 < n_groups) ++lg;
+      ++lg;
     }
     return ro;
   };
   const int n_rows = n_groups * (s1 - s0);
+  auto in_row = [&](uint32_t ro, uint32_t t) { return ro == kNone ? 0u : ro + t; };
   auto rows_done = [&](const Acc(&a)[kRows], int i) {
     if constexpr (kFlt) {
 #pragma unroll
@@ -352,7 +357,7 @@ __device__ __forceinline__ void unit_task(const UnitDesc& D, uint32_t unit, int 
     constexpr int E = N - 1;
     Raw x[E];
     auto load = [&]() {
-      G1* q = (G1*)(base + next_row());
+      G1* q = (G1*)(base + in_row(next_row(), 0u));
 #pragma unroll
       for (int e = 0; e < E; ++e) x[e] = q[e < eL ? e : 0];
     };
@@ -382,7 +387,7 @@ __device__ __forceinline__ void unit_task(const UnitDesc& D, uint32_t unit, int 
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
       ro[u] = next_row();
-      x[u] = vector(base, ro[u] + min(first_t, end_t));
+      x[u] = vector(base, in_row(ro[u], min(first_t, end_t)));
     }
   };
   first();
@@ -397,7 +402,7 @@ __device__ __forceinline__ void unit_task(const UnitDesc& D, uint32_t unit, int 
 #pragma unroll
       for (int u = 0; u < kRows; ++u) {
         R.vec(a[u], x[u], t);
-        x[u] = vector(base, ro[u] + min(t + pass, end_t));
+        x[u] = vector(base, in_row(ro[u], min(t + pass, end_t)));
       }
     }
 #pragma unroll
