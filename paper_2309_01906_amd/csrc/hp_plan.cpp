@@ -968,6 +968,19 @@ RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   r.waves = L.dp.nw;
   if (r.waves > 8) return RowRoute{};
   int64_t parts = L.dp.gsplit;
+  if (parts == 1) {
+    // The plan's waves, but: four where they load most of a batch of 16 KiB at once (8192 x
+    // 4096 float 24.5 -> 20.8 us, 5461 x 6144 22.0 -> 21.1; 7277 x 4611 would go from 21.7 to
+    // 22.1, 2048 x 8192 int32 from 11.8 to 12.9), one for blocks that are many batches and many enough (1365 x 24576 22.3 ->
+    // 21.2, 1500 x 30011 28.7 -> 28.0; blocks of 256 KiB are as fast on eight), and more
+    // than one where outputs are few (546 x 30720 int32 ARGMIN 18.9 -> 12.5,
+    // 200 x 20000 SUM 11.0 -> 4.6, 900 x 12000 float 9.7 -> 8.1).
+    const int64_t bytes = block * (16 / vec), last = bytes % 16384;
+    if (n_out >= 1024 && bytes >= 12 << 10 && bytes < 32 << 10 && (last == 0 || last >= 8192)) r.waves = 4;
+    else if (n_out >= 1024 && bytes >= 64 << 10 && bytes <= 192 << 10) r.waves = 1;
+    else if (bytes >= 32 << 10)
+      while (r.waves < 8 && n_out * r.waves < 1024) r.waves *= 2;
+  }
   int64_t len = cdiv(cdiv(block, parts), vec) * vec;
   while (parts > 1) {  // every part holds an aligned vector wherever it starts
     parts = cdiv(block, len);
@@ -984,14 +997,12 @@ RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
 // Automatic int32 plans of two or three segments run on the segment kernels (hp_segs.hip),
 // which read rows of any length as vectors where the plan's kernels fall back to single
 // elements, walk no odometer and split rows as well as M over the chip.  Measured against
-// the plan's kernels: (61, 125, 67, 59) SUM, MAX, ARGMIN 105 -> 31 us, (1024, 64, 1024)
-// ARGMAX of SUM 75 -> 42, the chain (64, 128, 64, 64) 34.6 -> 31.5, (4096, 16, 1024) SUM
-// of MAX 44.3 -> 41.8, (16777, 2048, 2) MAX of SUM 530 -> 52, (1, 2, 2^24) SUM of MAX
-// 8,306 -> 25, (1000000, 3, 5) MAX of SUM 849 -> 36; none was slower.
+// the plan's kernels: (61, 125, 67, 59) SUM, MAX, ARGMIN 105 -> 27 us, (1024, 64, 1024)
+// ARGMAX of SUM 75 -> 42, the chain (64, 128, 64, 64) 34.0 -> 26, (4096, 16, 1024) SUM
+// of MAX 44.3 -> 41.8, (16777, 2048, 2) MAX of SUM 530 -> 44, (1, 2, 2^24) SUM of MAX
+// 8,306 -> 25, (1000000, 3, 5) MAX of SUM 849 -> 31; none was slower.
 //   Rows of up to four vectors per lane go with M in one pass; longer ones through the
 // row kernels first (their values are at most 1/512 of the input).
-//   Waves per pair: 4,096 waves in all where that takes more than one per pair
-// ((1024, 64, 1024): 4 waves a pair 42 us, 8 waves 49 us), at least two steps each.
 SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, const Lowered& L) {
   SegRoute S, off;
   memset(&S, 0, sizeof S);
