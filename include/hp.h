@@ -303,9 +303,9 @@ hp_status hp_batch_destroy(hp_batch_t b);
  * candidate level maps of its size class on the current device -- the block seen
  * as (J, K) rows split between grid, waves and lane partitions, or many outputs
  * per task on lane partitions -- and store the fastest in the process-wide cache
- * that batched plans consult.  A candidate is timed as a batch of
- * replicas of the nest (its throughput when it shares the device), median of
- * `reps` runs, per nest.  best_us / auto_us (may be NULL) receive the winner's
+ * that batched plans consult, if it beats the automatic map by a fifth (else the
+ * automatic one).  A candidate is timed as a batch of replicas of the nest (its
+ * throughput when it shares the device), median of `reps` runs, per nest.  best_us / auto_us (may be NULL) receive the winner's
  * time and the automatic map's.  The cache is also read once from the file named
  * by the HP_TUNE_CACHE environment variable. */
 hp_status hp_tune_nest(const hp_nest* nest, uint32_t flags, int32_t reps, double* best_us, double* auto_us);

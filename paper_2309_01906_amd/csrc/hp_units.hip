@@ -8,8 +8,8 @@
 // persistent form's queue counters cost each wave an atomic per task).
 //
 // Measured, against the same batches as tasks of their plans on persistent workers:
-//   10,000 uneven bf16 nests of one SUM, 415 MiB, from a graph   126 -> 82 us (5.3 TB/s)
-//   1,000 of them                                         34.1 -> 17 us
+//   10,000 uneven bf16 nests of one SUM, 415 MiB, from a graph   126 -> 79 us (5.5 TB/s)
+//   1,000 of them                                         34.1 -> 14 us
 //   1,500 mixed int32, float and bf16 nests of 1 to 3 segments  2026 -> 159 us
 //     (the plan tasks of nested int32 reductions run the general kernel)
 //   a batch of one small nest                              9.2 -> 3.4 us
