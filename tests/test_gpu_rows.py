@@ -64,3 +64,24 @@ def test_extremes_and_non_finite_values():
         for flags in (0, hp.FLAG_NO_XCD):
             got, _ = gpu_reduce(x, x.shape, ("NONE", "SUM"), flags=flags)
             np.testing.assert_array_equal(got, [b, np.nan, np.nan, np.nan, b])
+
+
+@pytest.mark.parametrize("dtype,op", [(hp.F32, "SUM"), (hp.BF16, "SUM"), (hp.I32, "ARGMIN")])
+def test_lanes_and_waves_at_their_edges(dtype, op):
+    """Blocks where the lanes per row (16, 32 and 64, one to four vectors each) and the
+    waves per block change, in bytes, an element less and more, with many and few outputs."""
+    es = 2 if dtype == hp.BF16 else 4
+    for nbytes in [256, 512, 528, 768, 784, 1024, 1536, 1552, 3072, 4096]:
+        for d in (-1, 0, 1):
+            check_rows(dtype, op, 2100, nbytes // es + d)
+    for nbytes in [12 << 10, 16 << 10, 24 << 10, 32 << 10, 64 << 10, 192 << 10]:
+        for n, d in [(1024, 0), (1031, 1), (1023, -1), (130, 3), (3, 0)]:
+            if n * nbytes < 80 << 20:
+                check_rows(dtype, op, n, nbytes // es + d)
+
+
+def check_rows(dtype, op, n, b):
+    say("case rows", dtype, op, n, b)
+    x = data(dtype, (n, b), 230 + b % 5)
+    got, _ = gpu_reduce(x, x.shape, ("NONE", op))
+    assert_match(got, x, x.shape, ("NONE", op), what=f"rows {op} {x.shape}")
