@@ -90,8 +90,11 @@ struct KeyM {
     if (minlike) return key_minmax<true>(a, vm, vm, lane);
     return key_minmax<false>(a, vm, vm, lane);
   }
+  // (a wave without a row holds the identity, whose bits would unpack to a value and index
+  // that win against rows of the extreme value)
   __device__ __forceinline__ IAcc pair(Acc a) const {
     if (!arg) return IAcc{a, 0, 0};
+    if (a == identity()) return IntT::identity(op);
     return IAcc{a >> shift, (int)((minlike ? a : ~a) & mask), 0};
   }
 };

@@ -110,3 +110,18 @@ def test_arg_of_extreme_sums():
             for op in ["ARGMIN", "ARGMAX"]:
                 got, _ = gpu_reduce(x, ext, ("NONE", op, "SUM"))
                 assert_match(got, x, ext, ("NONE", op, "SUM"), what=f"sums {ext} {op}")
+
+
+@pytest.mark.parametrize("fill,mm", [(np.iinfo(np.int32).max, "MIN"), (np.iinfo(np.int32).min, "MAX")])
+def test_extreme_rows_beside_waves_without_steps(fill, mm):
+    """A part with fewer steps than its workgroup has waves leaves waves without a row: their
+    empty carrier ties with rows that hold the extreme value, and must not win."""
+    for ext in [(1, 16388, 64), (1, 177, 1000), (3, 177, 1000), (1, 3355, 64), (1, 4001, 1000), (2, 10, 1000), (1, 2, 3355, 64),
+                (2, 3, 177, 1000), (3, 2, 40001, 3)]:
+        x = np.full(ext, fill, np.int32)
+        for arg in ["ARG" + mm, mm]:
+            for child in ["MIN", "MAX", "ARGMIN"]:
+                for outer in [("SUM",), ("ARGMIN",), ("MIN",)] if len(ext) == 4 else [()]:
+                    ops = ("NONE",) + outer + (arg, child)
+                    got, _ = gpu_reduce(x, ext, ops)
+                    assert_match(got, x, ext, ops, what=f"extremes {ext} {ops}")
