@@ -90,11 +90,10 @@ struct KeyM {
     if (minlike) return key_minmax<true>(a, vm, vm, lane);
     return key_minmax<false>(a, vm, vm, lane);
   }
-  // (a wave without a row holds the identity, whose bits would unpack to a value and index
-  // that win against rows of the extreme value)
+  // of a carrier with at least one row: the identity's bits would unpack to a value and
+  // index that win against rows of the extreme value
   __device__ __forceinline__ IAcc pair(Acc a) const {
     if (!arg) return IAcc{a, 0, 0};
-    if (a == identity()) return IntT::identity(op);
     return IAcc{a >> shift, (int)((minlike ? a : ~a) & mask), 0};
   }
 };
@@ -238,10 +237,11 @@ __global__ void __launch_bounds__(NW* kWave)
     for (; s + U * NW < s1; s += U * NW) seg_round<OP, K, U, true>(row, x, lane, U, next, done);
     seg_round<OP, K, U, false>(row, x, lane, (s1 - s + NW - 1) / NW, next, done);
   }
-  // the wave's lane groups, then its workgroup's waves
+  // the wave's lane groups, then its workgroup's waves (the last part of a pair may have
+  // fewer steps than waves)
   acc = M.lanes(acc, lb, 6, lane);
   __shared__ IAcc slot[NW];
-  if (lane == 0) slot[w] = M.pair(acc);
+  if (lane == 0) slot[w] = s0 < s1 ? M.pair(acc) : IntT::identity(S.opM);
   __syncthreads();
   if (w != 0 || lane != 0) return;
   IAcc a = slot[0];
