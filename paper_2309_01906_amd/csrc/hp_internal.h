@@ -141,6 +141,8 @@ struct RowRoute {
 // How hp_run launches an automatic int32 plan of two or three reducing segments
 // (hp_segs.hip): out[o] = Q over q < eQ of M over m < eM of L over rows of eL elements.
 enum SegKind : int32_t { SEGS_OFF = 0, SEGS_SHORT, SEGS_LONG };
+constexpr int kTailThreads = 1024;  // threads of a workgroup that ends an output (fewer where it has fewer entries)
+constexpr int kTailLane = 8;        // up to so many entries per iteration of Q: a lane each, else a wave
 struct SegRoute {
   int32_t kind;
   int32_t opQ, opM, opL;
@@ -158,6 +160,9 @@ struct SegRoute {
   uint32_t parts;     // short: workgroups per pair
   uint32_t units;     // short: pairs * parts
   int32_t tail;       // short: the pairs' carriers go to ws and the tail kernel ends the nest
+  uint32_t tail_parts;  // workgroups per output in the tail (1: one ends it)
+  int32_t tail_per;     // iterations of Q, or of M without Q, per part of the tail
+  uint64_t tail_off;    // where the parts' carriers lie in ws
   RowRoute rows;      // long: the pass that reduces every row to a value
   uint64_t parts_off; // long: where that pass keeps the partials of split rows in ws
   uint64_t ws_bytes;

@@ -994,6 +994,29 @@ RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   return r;
 }
 
+// The tail's parts.  A workgroup ends an output in `passes` rounds of memory latency, some
+// 0.5 us each; parts cost a third launch, 2.7 us, and the more outputs the less they give
+// (3 x 16384 x 4 x 16, 16 rounds: 21.4 us, 15.1 in parts; 128 x 6114 x 4 x 4, 6 rounds:
+// 26.7 us, 28.5 in parts).  1 x 1048576 x 4 x 8 SUM, MAX, SUM: 570 us on one workgroup, 47 in
+// parts, 67 by the plan's kernels; 1 x 131072 x 8 x 64 SUM, MAX, ARGMIN: 123, 56 and 63; 2 x
+// 512 x 10 x 1257 MIN, MAX, ARGMIN: 62, 19 and 52.
+static void split_tail(SegRoute& S, int64_t n) {
+  int64_t passes, all = S.eQ;
+  if (S.opQ == HP_OP_NONE) passes = cdiv(n, 4 * kTailThreads), all = n;
+  else if (n <= kTailLane) passes = cdiv(S.eQ, kTailThreads) * (1 + n / 4);
+  else passes = cdiv(S.eQ, kTailThreads / kWave) * cdiv(n, 4 * kWave);
+  S.tail_parts = 1;
+  if (passes <= (S.n_out <= 4 ? 6 : 12)) return;
+  int64_t parts = cdiv(passes, 2);
+  const int64_t most = cdiv(1024, S.n_out);
+  if (parts > most) parts = most;
+  if (parts <= 1) return;
+  S.tail_per = (int32_t)cdiv(all, parts);
+  S.tail_parts = (uint32_t)cdiv(all, S.tail_per);
+  S.tail_off = (uint64_t)cdiv((int64_t)S.ws_bytes, 256) * 256;
+  S.ws_bytes = S.tail_off + (uint64_t)S.n_out * S.tail_parts * kSlotBytes;
+}
+
 // Automatic int32 plans of two or three segments run on the segment kernels (hp_segs.hip),
 // which read rows of any length as vectors where the plan's kernels fall back to single
 // elements, walk no odometer and split rows as well as M over the chip.  Measured against
@@ -1067,6 +1090,7 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
     S.kind = SEGS_LONG;
     S.parts_off = (uint64_t)cdiv(rows * 8, 256) * 256;
     S.ws_bytes = S.parts_off + (parts > 1 ? (uint64_t)rows * parts * 8 : 0);
+    split_tail(S, S.eM);
     return S;
   }
   if ((int64_t)S.eM * S.eL > ((int64_t)1 << 28)) return off;  // 32-bit byte offsets inside a pair
@@ -1127,6 +1151,7 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   if (S.tail && parts == 1 && (int64_t)S.eM * S.eL < 8 && pairs > (1 << 18)) return off;
   S.ws_bytes = S.tail ? (uint64_t)S.units * kSlotBytes : 0;
   S.kind = SEGS_SHORT;
+  if (S.tail) split_tail(S, parts);
   return S;
 }
 

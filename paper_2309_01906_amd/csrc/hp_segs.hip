@@ -303,42 +303,50 @@ __global__ void __launch_bounds__(256)
   seg_round<OP, K, U, false>(row, x, lane, n, next, done);
 }
 
-// Output o on one workgroup: for every q, the eM entries (o, q, m) -- carriers of M
-// (PARTS: the parts of its rows) or its child values -- then Q over q.  A wave takes
-// every NW-th q, or all waves share one when there is only one.
-template <class In, bool PARTS>
+// Part `part` of output o on one workgroup: for every q, the n entries (o, q, m) --
+// carriers of M (PARTS: the parts of its rows) or its child values -- then Q over q.  A
+// wave takes every NW-th q, a lane one of few entries, or all waves share one where there
+// is no Q.  One of several parts takes `per` iterations of Q (without Q, entries) and
+// leaves its carrier for a second pass over the parts; without that, a few outputs of a
+// long outermost level are a few workgroups' serial work: 1 x 1048576 x 4 x 8 SUM, MAX,
+// SUM took 570 us, where the input is read in 25.
+template <class In, bool PARTS, bool SPLIT>
 __global__ void __launch_bounds__(1024) k_seg_tail(const In* __restrict__ ws, void* __restrict__ out, int eQ, int n, int opQ,
-                                                   int opM, int out64) {
+                                                   int opM, int out64, uint32_t parts, int per,
+                                                   IAcc* __restrict__ carriers) {
   const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6), nw = (int)(blockDim.x >> 6);
-  const long long o = blockIdx.x;
-  const In* p = ws + o * eQ * n;
+  const uint32_t o = SPLIT ? blockIdx.x / parts : blockIdx.x;
+  const int i0 = SPLIT ? (int)(blockIdx.x - o * parts) * per : 0;  // its first iteration of Q, or entry
+  const In* p = ws + (long long)o * eQ * n;
   __shared__ IAcc slot[16];
   auto add = [&](IAcc& a, In x, int m) {
     if constexpr (PARTS) a = IntT::merge(a, x, opM);
     else outer_add(a, (long long)x, m, opM, true);
   };
   constexpr int U = 4;
-  auto span = [&](const In* r, int first, int stride) {  // this lane's entries of one q
+  auto span = [&](const In* r, int first, int stride, int end) {  // this lane's entries of one q
     IAcc a = IntT::identity(opM);
-    for (int m0 = first; m0 < n; m0 += U * stride) {
+    for (int m0 = first; m0 < end; m0 += U * stride) {
       In x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = r[m0 + u * stride < n ? m0 + u * stride : m0];
+      for (int u = 0; u < U; ++u) x[u] = r[m0 + u * stride < end ? m0 + u * stride : m0];
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (m0 + u * stride < n) add(a, x[u], m0 + u * stride);
+        if (m0 + u * stride < end) add(a, x[u], m0 + u * stride);
     }
     return a;
   };
+  const int all = opQ == HP_OP_NONE ? n : eQ;
+  const int i1 = SPLIT && i0 + per < all ? i0 + per : all;
   IAcc r;
   int op;
   if (opQ == HP_OP_NONE) {  // M alone: the whole workgroup on its entries
-    r = span(p, (int)threadIdx.x, (int)blockDim.x);
+    r = span(p, i0 + (int)threadIdx.x, (int)blockDim.x, i1);
     op = opM;
-  } else if (n <= 8) {  // few entries per q: a lane per q
+  } else if (n <= kTailLane) {  // few entries per q: a lane per q
     r = IntT::identity(opQ);
     op = opQ;
-    for (int q = (int)threadIdx.x; q < eQ; q += (int)blockDim.x) {
+    for (int q = i0 + (int)threadIdx.x; q < i1; q += (int)blockDim.x) {
       IAcc a = IntT::identity(opM);
       for (int m = 0; m < n; ++m) add(a, p[(long long)q * n + m], m);
       outer_add(r, IntT::emit(a, opM), q, opQ, true);
@@ -346,8 +354,8 @@ __global__ void __launch_bounds__(1024) k_seg_tail(const In* __restrict__ ws, vo
   } else {  // a wave per q
     r = IntT::identity(opQ);
     op = opQ;
-    for (int q = w; q < eQ; q += nw) {
-      IAcc a = span(p + (long long)q * n, lane, 64);
+    for (int q = i0 + w; q < i1; q += nw) {
+      IAcc a = span(p + (long long)q * n, lane, 64, n);
 #pragma unroll
       for (int b = 0; b < 6; ++b) a = IntT::merge(a, iacc_shfl(a, b, lane), opM);
       outer_add(r, IntT::emit(a, opM), q, opQ, true);
@@ -363,6 +371,10 @@ __global__ void __launch_bounds__(1024) k_seg_tail(const In* __restrict__ ws, vo
     for (int j = 1; j < nw; ++j) r = IntT::merge(r, slot[j], op);
   }
   if (lane == 0) {
+    if constexpr (SPLIT) {
+      carriers[blockIdx.x] = r;
+      return;
+    }
     const long long v = IntT::emit(r, op);
     if (out64) reinterpret_cast<long long*>(out)[o] = v;
     else reinterpret_cast<int*>(out)[o] = (int)v;
@@ -417,27 +429,41 @@ __global__ void __launch_bounds__(256) k_seg_tail_lane(const In* __restrict__ ws
 }
 
 template <class In, bool PARTS>
-void tail(const SegRoute& S, int n, const In* ws, void* out, hipStream_t st) {
+void tail(const SegRoute& S, int n, const In* ws, void* out, unsigned char* base, hipStream_t st) {
   const long long per = (long long)S.eQ * n;
   if (per <= 64 && S.n_out >= 4096) {
     hipLaunchKernelGGL((k_seg_tail_lane<In, PARTS>), dim3((unsigned)((S.n_out + 255) / 256)), dim3(256), 0, st, ws, out,
                        (long long)S.n_out, S.eQ, n, S.opQ, S.opM, S.out64);
     return;
   }
-  const unsigned threads = per <= 64 ? 64 : per <= 1024 ? 256 : 1024;
-  hipLaunchKernelGGL((k_seg_tail<In, PARTS>), dim3((unsigned)S.n_out), dim3(threads), 0, st, ws, out, S.eQ, n, S.opQ, S.opM,
-                     S.out64);
+  unsigned threads = per <= 64 ? 64 : per <= 1024 ? 256 : kTailThreads;
+  if (S.opQ != HP_OP_NONE && n > kTailLane) {  // a wave per iteration of Q
+    const int q = S.tail_parts > 1 ? S.tail_per : S.eQ;
+    threads = q < kTailThreads / kWave ? (unsigned)(q * kWave) : kTailThreads;
+  }
+  if (S.tail_parts == 1) {
+    hipLaunchKernelGGL((k_seg_tail<In, PARTS, false>), dim3((unsigned)S.n_out), dim3(threads), 0, st, ws, out, S.eQ, n, S.opQ,
+                       S.opM, S.out64, 1u, 0, (IAcc*)nullptr);
+    return;
+  }
+  IAcc* carriers = reinterpret_cast<IAcc*>(base + S.tail_off);
+  hipLaunchKernelGGL((k_seg_tail<In, PARTS, true>), dim3((unsigned)S.n_out * S.tail_parts), dim3(threads), 0, st, ws, out,
+                     S.eQ, n, S.opQ, S.opM, S.out64, S.tail_parts, S.tail_per, carriers);
+  const unsigned last = S.tail_parts <= 64 ? 64 : S.tail_parts <= 256 ? 256 : kTailThreads;
+  hipLaunchKernelGGL((k_seg_tail<IAcc, true, false>), dim3((unsigned)S.n_out), dim3(last), 0, st, carriers, out, 1,
+                     (int)S.tail_parts, (int)HP_OP_NONE, S.opQ == HP_OP_NONE ? S.opM : S.opQ, S.out64, 1u, 0, (IAcc*)nullptr);
 }
 
 }  // namespace
 
 hp_status launch_segs(const SegRoute& S, const void* in, void* out, void* ws, hipStream_t st) {
   const int32_t* x = reinterpret_cast<const int32_t*>(in);
+  unsigned char* base = reinterpret_cast<unsigned char*>(ws);
   if (S.kind == SEGS_LONG) {
-    const hp_status s = launch_rows(S.rows, in, ws, reinterpret_cast<unsigned char*>(ws) + S.parts_off, st);
+    const hp_status s = launch_rows(S.rows, in, ws, base + S.parts_off, st);
     if (s != HP_OK) return s;
-    if (S.rows.op == HP_OP_SUM) tail<long long, false>(S, S.eM, reinterpret_cast<const long long*>(ws), out, st);
-    else tail<int, false>(S, S.eM, reinterpret_cast<const int*>(ws), out, st);
+    if (S.rows.op == HP_OP_SUM) tail<long long, false>(S, S.eM, reinterpret_cast<const long long*>(ws), out, base, st);
+    else tail<int, false>(S, S.eM, reinterpret_cast<const int*>(ws), out, base, st);
   } else {
     IAcc* w = reinterpret_cast<IAcc*>(ws);
     switch (S.opL) {
@@ -447,7 +473,7 @@ hp_status launch_segs(const SegRoute& S, const void* in, void* out, void* ws, hi
       case HP_OP_ARGMAX: rows_op<HP_OP_ARGMAX>(S, x, out, w, st); break;
       default: rows_op<HP_OP_SUM>(S, x, out, w, st); break;
     }
-    if (S.tail) tail<IAcc, true>(S, (int)S.parts, w, out, st);
+    if (S.tail) tail<IAcc, true>(S, (int)S.parts, w, out, base, st);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HP_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));

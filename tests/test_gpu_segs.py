@@ -125,3 +125,19 @@ def test_extreme_rows_beside_waves_without_steps(fill, mm):
                     ops = ("NONE",) + outer + (arg, child)
                     got, _ = gpu_reduce(x, ext, ops)
                     assert_match(got, x, ext, ops, what=f"extremes {ext} {ops}")
+
+
+@pytest.mark.parametrize("ext,ops", [
+    ((1, 40000, 3, 5), ("ARGMIN", "MAX", "SUM")), ((3, 20011, 2, 8), ("SUM", "ARGMAX", "MIN")),      # a lane per iteration of Q
+    ((1, 100, 5000, 64), ("ARGMAX", "MIN", "SUM")), ((2, 512, 10, 1257), ("ARGMIN", "MAX", "ARGMIN")),  # a wave per iteration
+    ((1, 5000, 2, 1030), ("MAX", "ARGMIN", "SUM")), ((1, 20000, 1030), ("ARGMAX", "MIN")), ((2, 17001, 1030), ("MIN", "SUM")),
+    ((70, 9001, 1, 7), ("ARGMAX", "ARGMIN", "MAX"))])
+def test_tail_in_parts(ext, ops):
+    """Outermost levels that several workgroups of the tail share: ties across the parts,
+    and the extreme value everywhere."""
+    check(ext, ("NONE",) + ops, -2, 2, 360)
+    check(ext, ("NONE",) + ops, -(1 << 31), (1 << 31) - 1, 361)
+    fill = np.iinfo(np.int32).max if "MIN" in ops[0] else np.iinfo(np.int32).min
+    x = np.full(ext, fill, np.int32)
+    got, _ = gpu_reduce(x, ext, ("NONE",) + ops)
+    assert_match(got, x, ext, ("NONE",) + ops, what=f"extremes {ext} {ops}")

@@ -1,0 +1,52 @@
+"""Which kernels automatic plans and batched nests take, and with what partition: the
+planner's route functions, compiled for the host."""
+import math
+import os
+import subprocess
+
+import pytest
+
+import paper_2309_01906_amd as hp
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2309_01906_amd", "csrc")
+
+
+@pytest.fixture(scope="session")
+def probe(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "route_probe")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(HERE, "route_probe.cpp"), os.path.join(CSRC, "hp_plan.cpp"),
+                    os.path.join(CSRC, "hp_units.cpp"), "-o", exe], check=True)
+
+    def routes(nests, dtype=hp.I32):
+        text = "".join(f"{len(e)} " + " ".join(f"{x}:{hp._op(o)}" for x, o in zip(e, ("NONE",) + ops)) + f" {dtype}\n"
+                       for e, ops in nests)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(out) == len(nests)
+        return [dict(zip(w[::2], map(int, w[1::2]))) for w in map(str.split, out)]
+    return routes
+
+
+LONG_TAILS = [((1, 131072, 8, 64), ("SUM", "MAX", "ARGMIN")), ((1, 1048576, 4, 8), ("SUM", "MAX", "SUM")),
+              ((16, 131072, 4, 8), ("SUM", "MAX", "SUM")), ((2, 100000, 16, 20), ("MAX", "SUM", "ARGMIN")),
+              ((1, 1000, 10, 1100), ("MAX", "SUM", "MIN")), ((2, 512, 10, 1257), ("MIN", "MAX", "ARGMIN")),
+              ((1, 1000000, 1100), ("MAX", "SUM")), ((3, 40000, 2, 8), ("SUM", "MIN", "MAX")),
+              ((1, 100, 5000, 64), ("ARGMAX", "MIN", "SUM"))]
+
+
+def test_no_workgroup_ends_a_long_outermost_level_alone(probe):
+    """Few outputs with a long outermost level: the tail's work is shared, so that no
+    workgroup of it goes through more than a few rounds of memory latency."""
+    for (ext, ops), r in zip(LONG_TAILS, probe(LONG_TAILS)):
+        assert r["seg_kind"], ext
+        q, n = (ext[1], ext[2] if r["seg_kind"] == 2 else r["seg_parts"]) if len(ops) == 3 else (0, ext[1])
+        per = r["tail_per"] if r["tail_parts"] > 1 else (q or n)
+        rounds = math.ceil(per / 4096) if not q else math.ceil(per / 1024) * n if n <= 8 else math.ceil(per / 16) * math.ceil(n / 256)
+        assert rounds <= 16, (ext, r)
+        if r["tail_parts"] > 1:
+            assert (r["tail_parts"] - 1) * per < (q or n) <= r["tail_parts"] * per, (ext, r)
+            assert r["tail_off"] + ext[0] * r["tail_parts"] * 16 == r["seg_ws"]
+            carriers = ext[0] * q * n * 16 if r["seg_kind"] == 1 else math.prod(ext[:-1]) * 8
+            assert r["tail_off"] >= carriers and r["tail_off"] % 256 == 0
