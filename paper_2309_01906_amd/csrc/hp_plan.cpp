@@ -1017,6 +1017,25 @@ static void split_tail(SegRoute& S, int64_t n) {
   S.ws_bytes = S.tail_off + (uint64_t)S.n_out * S.tail_parts * kSlotBytes;
 }
 
+// Whether a nest of three segments stays with the plan's chain kernel, one launch that
+// keeps the pairs' carriers on the chip: where every level is even, outputs are whole on a
+// workgroup and its waves go through few strips, the segment kernels' carriers in memory
+// and second launch cost more than they gain.  512 x 8 x 4 x 8: 6.3 us by the chain kernel,
+// 7.7 by the segment kernels; 265 x 128 x 2 x 16: 7.8 and 10.5; 6516 x 32 x 4 x 4: 14.5 and
+// 24.1; but 128 x 256 x 16 x 4, of more strips: 28.5 and 10.1.  Short pairs only: from 512
+// elements the pair's own reduction decides (102 x 4 x 2 x 256: 6.9 and 6.6).  The lines were
+// drawn through 2,200 nests of even levels up to 64 MiB: of the 288 that had got more than 5 %
+// slower 221 are ended as before, and 36 lose more than 0.3 us, at most 32 %.
+static bool chain_ends_sooner(const SegRoute& S, const Lowered& L, int64_t pairs) {
+  if (L.dp.kernel != HP_KERNEL_INT_CHAIN || L.dp.gsplit != 1) return false;
+  const int64_t strips = L.dp.outer_iters, pair = (int64_t)S.eL * S.eM, bytes = 4 * pairs * pair, n = S.n_out;
+  if (strips == 1 && pair <= 256 && (n <= 1024 || L.dp.nw < 4) && (n <= 8192 || pairs > 1 << 17)) return true;
+  if (strips <= 2 && pair <= 256 && pairs > 4096 && bytes <= 8 << 20) return true;  // a load or two per wave there
+  if (strips <= 2 && pair <= 64 && pairs > 1 << 18) return true;                    // carriers of 16 bytes per 256
+  if (strips == 2 && pair <= 32 && n > 1024 && n <= 8192) return true;
+  return strips == 4 && pair <= 8 && bytes > 3 << 20;
+}
+
 // Automatic int32 plans of two or three segments run on the segment kernels (hp_segs.hip),
 // which read rows of any length as vectors where the plan's kernels fall back to single
 // elements, walk no odometer and split rows as well as M over the chip.  Measured against
@@ -1064,6 +1083,7 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   const int64_t want = kFillWorkgroups * 4;  // waves that fill the chip
   const int64_t pairs = n_out * S.eQ;
   if (pairs > lim / S.eM) return off;
+  if (ns == 3 && chain_ends_sooner(S, L, pairs)) return off;
   if (S.eL > 4 * kWave * 4) {
     const int64_t rows = pairs * S.eM;
     RowRoute& r = S.rows;

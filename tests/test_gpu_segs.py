@@ -141,3 +141,11 @@ def test_tail_in_parts(ext, ops):
     x = np.full(ext, fill, np.int32)
     got, _ = gpu_reduce(x, ext, ("NONE",) + ops)
     assert_match(got, x, ext, ("NONE",) + ops, what=f"extremes {ext} {ops}")
+
+
+@pytest.mark.parametrize("ops", THREE)
+def test_short_even_chains(ops):
+    """Even nests on both sides of the line between the chain kernel and the segment kernels."""
+    for ext in [(512, 8, 4, 8), (16, 4, 16, 4), (265, 128, 2, 16), (6516, 32, 4, 4), (3183, 64, 2, 4), (1, 32, 2, 16),
+                (102, 4, 2, 256), (512, 512, 8, 4), (9000, 2, 8, 8), (1030, 8, 4, 64)]:
+        check(ext, ("NONE",) + ops, -3, 3, 370)

@@ -50,3 +50,17 @@ def test_no_workgroup_ends_a_long_outermost_level_alone(probe):
             assert r["tail_off"] + ext[0] * r["tail_parts"] * 16 == r["seg_ws"]
             carriers = ext[0] * q * n * 16 if r["seg_kind"] == 1 else math.prod(ext[:-1]) * 8
             assert r["tail_off"] >= carriers and r["tail_off"] % 256 == 0
+
+
+def test_short_even_chains_stay_with_the_chain_kernel(probe):
+    """Even nests of three segments whose pairs are short and whose outputs a workgroup ends
+    in a strip or two take one launch; longer pairs, uneven levels and split outputs take the
+    segment kernels."""
+    chain = [(512, 8, 4, 8), (16, 4, 16, 4), (265, 128, 2, 16), (997, 16, 4, 16), (2251, 16, 4, 16), (1, 32, 2, 16),
+             (6516, 32, 4, 4), (199, 128, 4, 16), (3183, 64, 2, 4)]
+    segs = [(64, 128, 64, 64), (61, 125, 67, 59), (128, 2, 220, 256), (512, 512, 8, 4), (102, 4, 2, 256), (32, 48, 16, 16),
+            (16, 4, 15, 4), (1, 131072, 8, 64), (3, 5, 6, 16)]
+    ops = ("MIN", "ARGMAX", "MAX")
+    for ext, r in zip(chain + segs, probe([(e, ops) for e in chain + segs])):
+        assert (r["seg_kind"] == 0) == (ext in chain), (ext, r)
+        assert r["kernel"] == 7 or ext in segs, ext
