@@ -177,8 +177,10 @@ def kernel_name(inf: PlanInfo, ops=None) -> str:
         if inf.waves > 4:
             return f"hp::k_ordered_join<{w}>"
         n = min(block, 64 * max(inf.strips))  # elements of a wave
-        if w == 2 and n <= 512:
-            return "hp::k_ordered<2, 512, false>"
+        if n <= (512 if w == 2 else 256):
+            return "hp::k_ordered<2, 512, false>" if w == 2 else "hp::k_ordered<4, 256, false>"
+        if w == 4 and 512 < n <= 768 and inf.n_out * inf.gsplit > 1536:
+            return "hp::k_ordered<4, 256, true>"
         return f"hp::k_ordered<{w}, {2048 if w == 2 and -(-n // 2048) * 38 <= -(-n // 512) * 14 else 512}, true>"
     if inf.kernel == KERNEL_INT_CHAIN:
         return f"hp::k_nest_i32_chain<{OP_TEMPLATE[_op(ops[-1])] if ops else '?'}, {inf.nseg}>"

@@ -354,13 +354,20 @@ static void launch_w(const DevPlan& P, const u64* x, u64* y, u64* ws, hipStream_
   const long long units = n_out * C, span = P.ord_span;
   u64* dst = C > 1 ? ws : y;
   const dim3 grid = grid_of((units + 3) / 4);
-  // One group of 512 elements, or a loop over groups: of 2048 maps, which take 38
-  // multiplies (37 and one for the running product), or of 512, which take 14, whichever
-  // end a range with fewer; of 512 matrices only, since eight tiles' results spill
-  // (4,096 x 4,000: 94 us, 82 in groups of 512).
+  // One group of a tile (512 maps, 256 matrices), or a loop over groups: of 2048 maps, which
+  // take 38 multiplies (37 and one for the running product), or of 512, which take 14,
+  // whichever end a range with fewer; of 512 matrices only, since eight tiles' results spill
+  // (4,096 x 4,000: 94 us, 82 in groups of 512).  Blocks of up to 256 matrices are a tile's
+  // (17,657 x 89: 28.4 us in groups of 512, whose second tile is empty, 19.3 here), and
+  // three tiles go one by one where there are more than a wave and a half per SIMD (3,687 x
+  // 534: 16.3 and 15.2 us; 400 of them are 5 % faster in groups of two).
   const long long len = span < block ? span : block;
   if (W == 2 && len <= 512)
     hipLaunchKernelGGL((k_ordered<2, 512, false>), grid, dim3(256), 0, st, x, dst, units, C, block, span);
+  else if (W == 4 && len <= 256)
+    hipLaunchKernelGGL((k_ordered<4, 256, false>), grid, dim3(256), 0, st, x, dst, units, C, block, span);
+  else if (W == 4 && len > 512 && len <= 768 && units > 1536)
+    hipLaunchKernelGGL((k_ordered<4, 256, true>), grid, dim3(256), 0, st, x, dst, units, C, block, span);
   else if (W == 2 && (len + 2047) / 2048 * 38 <= (len + 511) / 512 * 14)
     hipLaunchKernelGGL((k_ordered<2, 2048, true>), grid, dim3(256), 0, st, x, dst, units, C, block, span);
   else

@@ -280,19 +280,23 @@ static hp_status lower_ordered(const hp_nest* n, const hp_level_map* map_in, uin
   for (int l = p; l < d; ++l) block *= n->extent[l];
   dp.n_out = n_out;
   dp.ord_block = block;
-  // Few blocks of up to 8 elements per thread of a workgroup are one workgroup's each (no
-  // second kernel: 4.4 us for 4,096 maps, 6.4 in chunks), and a block of up to 16 rows of
-  // 64 elements is a wave's.  Longer ones are cut into units of 8 rows, a tile of maps or
+  // Few short blocks are one workgroup's each (no second kernel: 4.4 us for 4,096 maps, 6.4
+  // in chunks), while the multiplies of one of its waves, more so beside others, take less
+  // than a launch (107 x 7,465 matrices: 29.4 us on workgroups, 9.3 in chunks; 62 x 8,052
+  // maps: 15.9 on workgroups, 9.8 in 64 parts of a wave each).  A block of up to 16 rows of
+  // 64 elements is a wave's, of maps up to 32 where they fill the chip (2,018 x 2,048: 13.2
+  // us in chunks, 10.7 whole).  Longer ones are cut into units of 8 rows, a tile of maps or
   // two of matrices: waves that come and go keep the chip more evenly busy than waves
   // that loop (300 x 20,011 maps: 18.4 us, 19.6 in 2048 units, 22.1 in 4096; 4,096 x
   // 16,384: 157 us, 165 in 4096 units).  At most 2048 units per output, for the second
   // kernel (4 x 4,000,000: 42.9 us, 47.3 with all 7,813), and 131,072 in all, whose
   // products take 4 MiB of workspace.
   const int64_t rows = cdiv(block, kWave);
+  const int64_t join_rows = n->dtype == HP_AFFINE64 ? (n_out <= 16 ? 96 : 80) : (n_out <= 64 ? 48 : 32);
   int64_t per = rows, C = 1;
-  if (p < d && rows > 1 && n_out <= 128 && rows <= 8 * kOrdJoinWaves) {
+  if (p < d && rows > 1 && n_out <= 128 && rows <= join_rows) {
     dp.nw = kOrdJoinWaves;
-  } else if (p < d && rows > 16 && n_out <= 65536) {
+  } else if (p < d && rows > (n->dtype == HP_AFFINE64 && n_out >= 1024 ? 32 : 16) && n_out <= 65536) {
     const int64_t most = n_out < 64 ? 2048 : 131072 / n_out;
     per = cdiv(cdiv(rows, most), 8) * 8;
     C = cdiv(rows, per);

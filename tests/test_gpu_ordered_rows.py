@@ -61,6 +61,16 @@ def test_chunks_and_many_outputs(kind, ext):
     check(kind, ext, 450, shift=48)
 
 
+@pytest.mark.parametrize("kind,ext", [
+    ("affine", (16, 6144)), ("affine", (16, 6145)), ("affine", (17, 5120)), ("affine", (17, 5121)), ("affine", (1024, 2048)),
+    ("affine", (1023, 2048)), ("affine", (1024, 2049)), ("mat2", (64, 3072)), ("mat2", (64, 3073)), ("mat2", (65, 2048)),
+    ("mat2", (65, 2049)), ("mat2", (300, 256)), ("mat2", (300, 257)), ("mat2", (1537, 513)), ("mat2", (1537, 768)),
+    ("mat2", (1537, 769)), ("mat2", (1536, 600))])
+def test_edges_of_the_forms(kind, ext):
+    say("case ordered edges", kind, ext)
+    check(kind, ext, 455, shift=32)
+
+
 def test_graph_replays():
     import torch
     for kind, ext in [("affine", (30, 40001)), ("mat2", (3, 5000)), ("affine", (500, 50))]:

@@ -64,3 +64,17 @@ def test_short_even_chains_stay_with_the_chain_kernel(probe):
     for ext, r in zip(chain + segs, probe([(e, ops) for e in chain + segs])):
         assert (r["seg_kind"] == 0) == (ext in chain), (ext, r)
         assert r["kernel"] == 7 or ext in segs, ext
+
+
+def test_ordered_blocks_leave_the_workgroup_in_time():
+    """A workgroup multiplies a block alone only while that is short: beyond, and with many
+    blocks, chunks or waves of their own."""
+    for dt, ext, joined in [(hp.AFFINE64, (16, 6144), True), (hp.AFFINE64, (17, 6144), False), (hp.AFFINE64, (17, 5120), True),
+                            (hp.AFFINE64, (62, 8052), False), (hp.AFFINE64, (129, 4096), False), (hp.MAT2X2_64, (64, 3072), True),
+                            (hp.MAT2X2_64, (65, 3072), False), (hp.MAT2X2_64, (6, 5742), False), (hp.MAT2X2_64, (107, 7465), False),
+                            (hp.MAT2X2_64, (128, 2048), True)]:
+        i = hp.inspect(ext, ("NONE", "PROD"), dt)
+        assert (i["waves"] == 16) == joined and (i["gsplit"] == 1) == joined, (ext, i)
+    assert hp.inspect((2018, 2048), ("NONE", "PROD"), hp.AFFINE64)["gsplit"] == 1
+    assert hp.inspect((1000, 2048), ("NONE", "PROD"), hp.AFFINE64)["gsplit"] == 4
+    assert hp.inspect((5941, 99), ("NONE", "PROD"), hp.MAT2X2_64)["kernel_name"] == "hp::k_ordered<4, 256, false>"
