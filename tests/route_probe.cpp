@@ -4,11 +4,19 @@
 #include <cstdio>
 
 #include "hp_internal.h"
+#include "hp_stencil_form.h"
 #include "hp_units.h"
 
 int main() {
   int depth;
   while (std::scanf("%d", &depth) == 1) {
+    if (depth == 0) {
+      long long rows, cols;
+      int sweeps;
+      if (std::scanf("%lld %lld %d", &rows, &cols, &sweeps) != 3) return 1;
+      std::printf("reg %d\n", (int)hp::reg_form(rows, cols, sweeps));
+      continue;
+    }
     hp_nest n{};
     n.depth = depth;
     for (int l = 0; l < depth; ++l) {

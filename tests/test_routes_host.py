@@ -21,10 +21,10 @@ def probe(tmp_path_factory):
                     os.path.join(CSRC, "hp_units.cpp"), "-o", exe], check=True)
 
     def routes(nests, dtype=hp.I32):
-        text = "".join(f"{len(e)} " + " ".join(f"{x}:{hp._op(o)}" for x, o in zip(e, ("NONE",) + ops)) + f" {dtype}\n"
+        text = nests if isinstance(nests, str) else "".join(f"{len(e)} " + " ".join(f"{x}:{hp._op(o)}" for x, o in zip(e, ("NONE",) + ops)) + f" {dtype}\n"
                        for e, ops in nests)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
-        assert len(out) == len(nests)
+        assert len(out) == (nests.count("\n") if text is nests else len(nests))
         return [dict(zip(w[::2], map(int, w[1::2]))) for w in map(str.split, out)]
     return routes
 
@@ -78,3 +78,14 @@ def test_ordered_blocks_leave_the_workgroup_in_time():
     assert hp.inspect((2018, 2048), ("NONE", "PROD"), hp.AFFINE64)["gsplit"] == 1
     assert hp.inspect((1000, 2048), ("NONE", "PROD"), hp.AFFINE64)["gsplit"] == 4
     assert hp.inspect((5941, 99), ("NONE", "PROD"), hp.MAT2X2_64)["kernel_name"] == "hp::k_ordered<4, 256, false>"
+
+
+def test_tall_stencils_of_one_or_two_strips_keep_their_tiles(probe):
+    """Two to four sweeps over a tall array of one or two strips of 248 columns, all of which
+    hold an edge, run in LDS tiles; shorter and wider arrays in registers."""
+    tiles = [(2516, 484, 2), (5091, 432, 2), (1024, 482, 2), (6675, 230, 2), (4096, 380, 3), (1315, 243, 3), (2048, 256, 4),
+             (8192, 8192, 1)]
+    regs = [(600, 484, 2), (1000, 230, 2), (2516, 700, 2), (1500, 380, 3), (1000, 243, 3), (2964, 286, 3), (1024, 500, 4), (4096, 398, 4), (8192, 8192, 4),
+            (1500, 1500, 8), (8192, 8192, 8)]
+    got = probe("".join(f"0 {r} {c} {t}\n" for r, c, t in tiles + regs))
+    assert [g["reg"] for g in got] == [0] * len(tiles) + [1] * len(regs)
