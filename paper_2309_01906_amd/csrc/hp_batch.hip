@@ -207,8 +207,8 @@ struct hp_batch_s {
   std::vector<hp::UnitDesc> units;      // host copy of the unit descriptors (pointers set by set_io)
   hp::UnitDesc* d_units = nullptr;      // in the arena
   int2* d_unit_folds = nullptr;         // in the arena
-  std::vector<int> unit_fold_beg;       // nest i's: [unit_fold_beg[i], unit_fold_beg[i + 1])
-  int n_unit_fold = 0;
+  std::vector<int> unit_fold_beg;       // nest i's: routes[i].folds from unit_fold_beg[i] on
+  int n_unit_fold = 0, n_shared_fold = 0;
   int n_plan_groups = 0;                // groups with task counters
   bool io_set = false;
   hipGraph_t graph = nullptr;
@@ -332,13 +332,16 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   const size_t unit_off = arena_bytes;
   if (b->n_plan_groups < (int)keys.size()) arena_bytes = align_up(arena_bytes + (size_t)n * sizeof(UnitDesc), 256);
   std::vector<int2> unit_folds;
-  b->unit_fold_beg.assign((size_t)n + 1, 0);
-  for (int64_t i = 0; i < n; ++i) {
-    b->unit_fold_beg[(size_t)i] = (int)unit_folds.size();
-    if (routes[(size_t)i].on)
-      for (int64_t o = 0; o < routes[(size_t)i].folds; ++o) unit_folds.push_back(make_int2((int)i, (int)o));
+  b->unit_fold_beg.assign((size_t)n, 0);
+  for (const int nw : {hp::kFoldWaves, 1}) {  // outputs that a workgroup shares first
+    for (int64_t i = 0; i < n; ++i) {
+      const UnitRoute& r = routes[(size_t)i];
+      if (!r.on || r.d.fold_waves != nw) continue;
+      b->unit_fold_beg[(size_t)i] = (int)unit_folds.size();
+      for (int64_t o = 0; o < r.folds; ++o) unit_folds.push_back(make_int2((int)i, (int)o));
+    }
+    if (nw > 1) b->n_shared_fold = (int)unit_folds.size();
   }
-  b->unit_fold_beg[(size_t)n] = (int)unit_folds.size();
   b->n_unit_fold = (int)unit_folds.size();
   const size_t unit_fold_off = arena_bytes;
   arena_bytes = align_up(arena_bytes + unit_folds.size() * sizeof(int2), 256);
@@ -519,7 +522,7 @@ static hp_status launch_groups(hp_batch_s* b, hipStream_t st) {
     if (s == HP_OK) s = hp::launch_batch(G.family, G.chunk, A, G.grid, hp::kBatchGroupWaves, G.lds, st);
     if (s != HP_OK) return s;
   }
-  const hp_status s = hp::launch_unit_folds(b->d_units, b->d_unit_folds, b->n_unit_fold, st);
+  const hp_status s = hp::launch_unit_folds(b->d_units, b->d_unit_folds, b->n_shared_fold, b->n_unit_fold, st);
   if (s != HP_OK || b->n_fold <= 0) return s;
   return hp::launch_fold(b->d_plans, b->d_fold, b->n_fold, b->d_out, b->d_ws, st,
                          reinterpret_cast<unsigned int*>(b->arena), b->n_plan_groups * hp::kCtrWords);
@@ -555,8 +558,10 @@ static hp_status launch_one(hp_batch_s* b, int64_t i, const void* in, void* out,
 
 // The fold of nest i alone.
 static hp_status launch_fold_of(hp_batch_s* b, int64_t i, hipStream_t st) {
-  const int u0 = b->unit_fold_beg[(size_t)i], u1 = b->unit_fold_beg[(size_t)i + 1];
-  if (u1 > u0) return hp::launch_unit_folds(b->d_units, b->d_unit_folds + u0, u1 - u0, st);
+  const hp::UnitRoute& r = b->routes[(size_t)i];
+  if (r.on && r.folds)
+    return hp::launch_unit_folds(b->d_units, b->d_unit_folds + b->unit_fold_beg[(size_t)i],
+                                 r.d.fold_waves > 1 ? (int)r.folds : 0, (int)r.folds, st);
   const int f0 = b->fold_beg[(size_t)i], f1 = b->fold_beg[(size_t)i + 1];
   if (f1 == f0) return HP_OK;
   return hp::launch_fold(b->d_plans, b->d_fold + f0, f1 - f0, b->d_out, b->d_ws, st);

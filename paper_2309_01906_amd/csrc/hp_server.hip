@@ -131,7 +131,7 @@ struct Layout {
   std::vector<size_t> task_off, ctr_off;
   std::vector<long long> ntask;
   std::vector<hp::FoldTask> folds;
-  long long n_unit_fold = 0;
+  long long n_unit_fold = 0, n_shared_fold = 0;
   std::vector<size_t> ws_off;
 };
 
@@ -294,13 +294,20 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
       D.out = r.out;
       D.ws = ws;
       hunit[k] = D;
-      for (long long o = 0; o < r.as_run.nfold; ++o) *hufold++ = make_int2((int)k, (int)o);
       continue;
     }
     hp_[k] = r.L.dp;
     hin[k] = r.in;
     hout[k] = r.out;
     hws[k] = ws;
+  }
+  for (const int nw : {kFoldWaves, 1}) {  // outputs that a workgroup shares first
+    for (int64_t i = 0; i < n; ++i) {
+      const Request& r = *rs[(size_t)i];
+      if (!r.unit.on || r.unit.d.fold_waves != nw) continue;
+      for (long long o = 0; o < r.as_run.nfold; ++o) *hufold++ = make_int2((int)Lo.at[(size_t)i], (int)o);
+    }
+    if (nw > 1) Lo.n_shared_fold = hufold - reinterpret_cast<int2*>(h + Lo.unit_fold_off);
   }
   std::vector<BatchArgs> args(Lo.keys.size());
   std::vector<int> grid(Lo.keys.size());
@@ -396,7 +403,8 @@ hp_status launch_slot(hp_server_s* S, Slot& slot, std::vector<Request*>& rs, boo
   if (Lo.n_unit_fold) {
     if ((s = hook(step)) != HP_OK) return s;
     s = launch_unit_folds(reinterpret_cast<const UnitDesc*>(d + Lo.unit_off),
-                          reinterpret_cast<const int2*>(d + Lo.unit_fold_off), (int)Lo.n_unit_fold, slot.st);
+                          reinterpret_cast<const int2*>(d + Lo.unit_fold_off), (int)Lo.n_shared_fold, (int)Lo.n_unit_fold,
+                          slot.st);
     if (s != HP_OK) {
       *drain = true;
       return s;

@@ -20,6 +20,16 @@ static inline int log2u(uint64_t x) {
 // carrier of M): short rows make smaller units.
 static constexpr int64_t kUnitCost = 24;
 
+// Rounds of a fold (fold_plan) from which the waves of a workgroup share an output (a
+// multiple where outputs fill the chip), and up to which that is worth it: a nest of more
+// stays with its plan's tasks, which split the outermost level over the chip; plan tasks that
+// read single elements are slower yet.  A batch of one nest (rounds of a workgroup): 1 x
+// 16384 x 8 x 64 SUM, MAX, ARGMIN (16) 180 us by one wave, 36 by sixteen, 67 as plan tasks; 4
+// x 64 x 16 x 1024 (4) 81, 15 and 51; 4 x 65536 x 4 x 16 (64) 90 by sixteen, 66 as plan
+// tasks; 1 x 65536 x 23 x 2 (64) 651, 75 and 926; 1 x 524288 x 4 x 5 (512) 485
+// by sixteen, 301 as plan tasks.
+static constexpr int64_t kLongFold = 4, kMostRounds = 40;
+
 UnitRoute unit_route(const hp_nest* n, uint32_t flags, const Lowered& L, bool tuned) {
   UnitRoute r, off;
   memset(&r, 0, sizeof r);
@@ -153,6 +163,17 @@ UnitRoute unit_route(const hp_nest* n, uint32_t flags, const Lowered& L, bool tu
     if (carriers && pair_bytes < 32 && carriers > (1 << 18)) return off;
   }
   D.partial = carriers ? 1 : 0;
+  D.fold_waves = 1;
+  if (carriers) {
+    const int64_t rows = D.lparts > 1 ? D.eM : 1, parts = D.lparts > 1 ? D.lparts : D.mparts;
+    FoldPlan f = fold_plan(ns == 3, D.eQ, rows, parts, 1);
+    if (f.rounds > (n_out <= 256 ? kLongFold : 8 * kLongFold)) {
+      D.fold_waves = kFoldWaves;
+      f = fold_plan(ns == 3, D.eQ, rows, parts, kFoldWaves);
+      if (f.rounds > (L.dp.chunk > 1 ? kMostRounds : 4 * kMostRounds)) return off;
+    }
+    D.fold_form = f.form;
+  }
   r.folds = carriers ? n_out : 0;
   r.ws_bytes = (uint64_t)carriers * kSlotBytes;
   r.dtype = n->dtype;

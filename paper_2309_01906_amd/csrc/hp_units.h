@@ -36,7 +36,9 @@ struct UnitDesc {
   int32_t out_kind;   // UnitOut
   int32_t partial;
   int32_t direct;     // one segment: a row's value is an output
-  int32_t pad[6];
+  int32_t fold_form;  // FoldForm
+  int32_t fold_waves; // 1 or kFoldWaves
+  int32_t pad[4];
 };
 static_assert(sizeof(UnitDesc) == 128, "one descriptor is one 128-byte line");
 
@@ -45,10 +47,36 @@ struct UnitRoute {
   int32_t dtype;
   UnitDesc d;        // pointers unset
   int64_t units;
-  int64_t folds;     // fold tasks
+  int64_t folds;     // fold tasks, one per output
   uint64_t ws_bytes;
   double unit_bytes; // input bytes of the largest unit, for the order of the tasks
 };
+
+// What is left of an output -- for eQ iterations of Q, `rows` groups of `parts` carriers
+// (rows: the iterations of M where rows were cut) -- is folded by a wave or, where that
+// would take long, by the kFoldWaves waves of a workgroup.  Each form takes so many rounds
+// of memory latency, some 0.8 us each.
+constexpr int kFoldWaves = 16;
+enum FoldForm : int32_t {
+  FOLD_LANE_Q = 0,  // a lane per iteration of Q
+  FOLD_LANE_ROW,    // a wave per iteration of Q, a lane per row
+  FOLD_WAVE         // a wave per iteration of Q, or per row without Q
+};
+struct FoldPlan {
+  int32_t form;
+  int64_t rounds;
+};
+inline FoldPlan fold_plan(bool hasQ, int64_t eQ, int64_t rows, int64_t parts, int64_t waves) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t lanes = 64 * waves, some = up(parts, 4);  // four loads in flight
+  const int64_t r = hasQ ? up(eQ, waves) * up(rows, 64) * some : up(rows, lanes) * some;
+  const int64_t w = hasQ ? up(eQ, waves) * rows * up(parts, 256) : rows > 1 ? up(rows, waves) * up(parts, 256) : up(parts, 4 * lanes);
+  if (hasQ) {
+    const int64_t q = up(eQ, lanes) * rows * some;
+    if (q <= r && q <= w) return FoldPlan{FOLD_LANE_Q, q};
+  }
+  return r < w ? FoldPlan{FOLD_LANE_ROW, r} : FoldPlan{FOLD_WAVE, w};
+}
 
 // The unit route of a batched nest whose plan is L.  tuned: L comes from the tuner cache,
 // whose grid (units per output or outputs per unit) and lanes per output are kept.

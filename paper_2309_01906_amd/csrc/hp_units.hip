@@ -448,12 +448,14 @@ __global__ void __launch_bounds__(256, kUnitWaves<Raw>) k_units_of(const UnitDes
   unit_any<Raw>(*(const UnitDesc*)((CDesc*)desc), (uint32_t)t, (int)(threadIdx.x & 63));
 }
 
-// The carriers of one output, a wave: for each q, `rows` groups of `parts` carriers of
-// `op` (rows: the iterations of M when rows were split, else 1).
-__device__ __forceinline__ void fold_ints(const UnitDesc& D, long long o, int lane) {
+// The carriers of one output: for each q, `rows` groups of `parts` carriers of `op` (rows:
+// the iterations of M when rows were split, else 1), by wave w of nw; the waves' carriers
+// meet in `slot`, and one lane ends the output.
+template <int nw>
+__device__ __forceinline__ void fold_ints(const UnitDesc& D, long long o, int lane, int w, IAcc* slot) {
   const bool cut = D.lparts > 1;
   const int rows = cut ? D.eM : 1, parts = cut ? D.lparts : D.mparts;
-  const int op = cut ? D.opL : D.opM, opM = D.opM, eQ = D.eQ;
+  const int op = cut ? D.opL : D.opM, opM = D.opM, eQ = D.eQ, inner = cut ? opM : op;
   // split rows: the child of M is the row's value; M of a single reduction passes it on
   const IAcc* p = reinterpret_cast<const IAcc*>(D.ws) + o * eQ * (long long)rows * parts;
   constexpr int U = 4;
@@ -473,70 +475,110 @@ __device__ __forceinline__ void fold_ints(const UnitDesc& D, long long o, int la
     IAcc c{IntT::emit(v, op), t, 0};
     m = IntT::merge(m, c, opM);
   };
-  auto all = [&](IAcc a, int o_) {
+  auto lanes = [&](IAcc a, int o_) {
 #pragma unroll
     for (int b = 0; b < 6; ++b) a = IntT::merge(a, IntT::shfl(a, 1 << b, lane), o_);
+    return a;
+  };
+  auto waves = [&](IAcc a, int o_) {  // a is the wave's, on every lane
+    if constexpr (nw > 1) {
+      if (lane == 0) slot[w] = a;
+      __syncthreads();
+      a = slot[0];
+      for (int j = 1; j < nw; ++j) a = IntT::merge(a, slot[j], o_);
+    }
     return a;
   };
   auto value = [&](IAcc m) {  // of one q
     return cut ? (D.direct ? m.v : IntT::emit(m, opM)) : IntT::emit(m, op);
   };
-  IAcc Q = IntT::identity(D.opQ);
-  long long v = 0;
-  const bool hasQ = D.opQ != HP_OP_NONE;
-  if (hasQ && rows * (long long)parts <= 4) {  // a lane per q
-    for (int q = lane; q < eQ; q += 64) {
-      IAcc m = IntT::identity(cut ? opM : op);
-      for (int a = 0; a < rows; ++a) {
-        const IAcc w = merged(p + ((long long)q * rows + a) * parts, 0, 1);
-        if (cut) child(m, w, a);
-        else m = w;
-      }
-      Q = IntT::merge(Q, IAcc{value(m), q, 0}, D.opQ);
+  // M over rows first, first + stride, ... of one q, on the wave's lanes or a row at a time
+  auto rows_of = [&](const IAcc* r, int first, int stride) {
+    IAcc m = IntT::identity(opM);
+    if (D.fold_form == FOLD_LANE_ROW) {
+      for (int a = first * 64 + lane; a < rows; a += stride * 64) child(m, merged(r + (long long)a * parts, 0, 1), a);
+      m = lanes(m, opM);
+    } else {
+      for (int a = first; a < rows; a += stride) child(m, lanes(merged(r + (long long)a * parts, lane, 64), op), a);
     }
-    Q = all(Q, D.opQ);
-    v = IntT::emit(Q, D.opQ);
+    return m;
+  };
+  long long v;
+  if (D.opQ == HP_OP_NONE) {
+    IAcc m;
+    if (!cut) m = waves(lanes(merged(p, w * 64 + lane, nw * 64), op), op);
+    else if (rows > 1) m = waves(rows_of(p, w, nw), opM);
+    else child(m = IntT::identity(opM), waves(lanes(merged(p, w * 64 + lane, nw * 64), op), op), 0);
+    v = value(m);
   } else {
-    for (int q = 0; q < eQ; ++q) {
-      const IAcc* r = p + (long long)q * rows * parts;
-      IAcc m = IntT::identity(cut ? opM : op);
-      if (!cut) {
-        m = all(merged(r, lane, 64), op);
-      } else if (parts >= 16) {  // the wave on one row's parts
-        for (int a = 0; a < rows; ++a) child(m, all(merged(r + (long long)a * parts, lane, 64), op), a);
-      } else {  // a lane per row
-        for (int a = lane; a < rows; a += 64) child(m, merged(r + (long long)a * parts, 0, 1), a);
-        m = all(m, opM);
+    IAcc Q = IntT::identity(D.opQ);
+    if (D.fold_form == FOLD_LANE_Q) {
+      for (int q = w * 64 + lane; q < eQ; q += nw * 64) {
+        IAcc m = IntT::identity(inner);
+        for (int a = 0; a < rows; ++a) {
+          const IAcc x = merged(p + ((long long)q * rows + a) * parts, 0, 1);
+          if (cut) child(m, x, a);
+          else m = x;
+        }
+        Q = IntT::merge(Q, IAcc{value(m), q, 0}, D.opQ);
       }
-      v = value(m);
-      if (hasQ) Q = IntT::merge(Q, IAcc{v, q, 0}, D.opQ);
+      Q = lanes(Q, D.opQ);
+    } else {
+      for (int q = w; q < eQ; q += nw) {
+        const IAcc* r = p + (long long)q * rows * parts;
+        const IAcc m = cut ? rows_of(r, 0, 1) : lanes(merged(r, lane, 64), op);
+        Q = IntT::merge(Q, IAcc{value(m), q, 0}, D.opQ);
+      }
     }
-    if (hasQ) v = IntT::emit(Q, D.opQ);
+    v = IntT::emit(waves(Q, D.opQ), D.opQ);
   }
-  if (lane == 0) out_int(D, o, v);
+  if (lane == 0 && w == 0) out_int(D, o, v);
 }
 
-__device__ __forceinline__ void fold_floats(const UnitDesc& D, long long o, int lane) {
+// Float partials, in an order that their number fixes.
+template <int nw>
+__device__ __forceinline__ void fold_floats(const UnitDesc& D, long long o, int lane, int w, DPair* slot) {
   const double* p = reinterpret_cast<const double*>(D.ws) + 2 * o * D.lparts;
   DPair a{0.0, 0.0};
-  for (int k = lane; k < D.lparts; k += 64) dpair_add(a, p[2 * k]);
+  constexpr int U = 4;
+  const int stride = nw * 64;
+  for (int k = w * 64 + lane; k < D.lparts; k += U * stride) {
+    double x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = k + u * stride < D.lparts ? p[2 * (k + u * stride)] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) dpair_add(a, x[u]);
+  }
 #pragma unroll
   for (int b = 0; b < 6; ++b) a = dpair_merge(a, DPair{xor_move_d(a.s, 1 << b, lane), xor_move_d(a.c, 1 << b, lane)});
+  if constexpr (nw > 1) {
+    if (lane == 0) slot[w] = a;
+    __syncthreads();
+    a = slot[0];
+    for (int j = 1; j < nw; ++j) a = dpair_merge(a, slot[j]);
+  }
   const double v = float_result(a.s + a.c);
-  if (lane != 0) return;
+  if (lane != 0 || w != 0) return;
   if (D.out_kind == UNIT_F32) reinterpret_cast<float*>(D.out)[o] = (float)v;
   else reinterpret_cast<double*>(D.out)[o] = v;
 }
 
-__global__ void __launch_bounds__(256) k_unit_folds(const UnitDesc* descs, const int2* tasks, int n) {
-  const int t = (int)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+// A fold task per wave (kShared: per workgroup, whose waves share it).  Tasks of a wave go
+// four to a workgroup, to spread a few hundred of them over the chip.
+template <bool kShared>
+__global__ void __launch_bounds__(kShared ? 64 * kFoldWaves : 256) k_unit_folds(const UnitDesc* descs, const int2* tasks, int n) {
+  constexpr int nw = kShared ? kFoldWaves : 1;
+  __shared__ IAcc slot[nw];
+  static_assert(sizeof(IAcc) == sizeof(DPair), "one slot for either");
+  const int w = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int t = kShared ? (int)blockIdx.x : (int)blockIdx.x * 4 + w;
   if (t >= n) return;
   CInt* e = (CInt*)tasks;
   const int nest = e[2 * (long long)t], o = e[2 * (long long)t + 1];
   const UnitDesc& D = *(const UnitDesc*)((CDesc*)descs + nest);
   const int lane = (int)(threadIdx.x & 63);
-  if (D.out_kind <= UNIT_F32) fold_floats(D, o, lane);
-  else fold_ints(D, o, lane);
+  if (D.out_kind <= UNIT_F32) fold_floats<nw>(D, o, lane, kShared ? w : 0, reinterpret_cast<DPair*>(slot));
+  else fold_ints<nw>(D, o, lane, kShared ? w : 0, slot);
 }
 
 hp_status launched() {
@@ -569,14 +611,18 @@ hp_status warm_unit_kernels(hipStream_t st) {
   hipLaunchKernelGGL(k_units<float>, one, wg, 0, st, nullptr, nullptr, 0);
   hipLaunchKernelGGL(k_units<uint16_t>, one, wg, 0, st, nullptr, nullptr, 0);
   hipLaunchKernelGGL(k_units<int32_t>, one, wg, 0, st, nullptr, nullptr, 0);
-  hipLaunchKernelGGL(k_unit_folds, one, wg, 0, st, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(k_unit_folds<false>, one, wg, 0, st, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(k_unit_folds<true>, one, dim3(64 * kFoldWaves), 0, st, nullptr, nullptr, 0);
   return launched();
 }
 
-hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n, hipStream_t st) {
-  if (n <= 0) return HP_OK;
-  hipLaunchKernelGGL(k_unit_folds, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, descs, tasks, n);
-  return launched();
+hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n_shared, int n, hipStream_t st) {
+  if (n_shared > 0)
+    hipLaunchKernelGGL(k_unit_folds<true>, dim3((unsigned)n_shared), dim3(64 * kFoldWaves), 0, st, descs, tasks, n_shared);
+  if (n > n_shared)
+    hipLaunchKernelGGL(k_unit_folds<false>, dim3((unsigned)((n - n_shared + 3) / 4)), dim3(256), 0, st, descs,
+                       tasks + n_shared, n - n_shared);
+  return n > 0 ? launched() : HP_OK;
 }
 
 }  // namespace hp

@@ -13,7 +13,8 @@ hp_status launch_units(int dtype, const UnitDesc* descs, const int2* tasks, int 
 hp_status launch_units_of(int dtype, const UnitDesc* desc, int n, hipStream_t st);
 // Load the unit kernels: each launched with no tasks.
 hp_status warm_unit_kernels(hipStream_t st);
-// The nests' partial carriers: n fold tasks (nest, output), a wave each.
-hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n, hipStream_t st);
+// The nests' partial carriers: n fold tasks (nest, output), the first n_shared on a workgroup
+// each (nests of kFoldWaves), the others on a wave.
+hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n_shared, int n, hipStream_t st);
 
 }  // namespace hp

@@ -153,3 +153,26 @@ def test_served_units_and_plan_tasks(slot_bytes):
                 assert_match(got, hosts[i], e, o, rel=1e-13, what=f"served {e} {o}")
                 if slot_bytes == 64 << 20:
                     np.testing.assert_array_equal(got, want[i])
+
+
+@pytest.mark.parametrize("flags", [0, hp.BATCH_GRAPH])
+def test_folds_that_a_workgroup_shares(flags):
+    """Outputs of many carriers beside ones of few: every form of the fold, at several waves
+    and at one, with ties and with the extreme value everywhere."""
+    shapes = [((2, 3000, 8, 64), ("ARGMIN", "MAX", "SUM")), ((1, 40000, 4, 8), ("SUM", "MAX", "SUM")),
+              ((3, 700, 40, 90), ("ARGMAX", "ARGMIN", "MAX")), ((1, 700000, 64), ("ARGMAX", "MIN")),
+              ((2, 90, 40000), ("SUM", "ARGMAX")), ((1, 4, 60, 30000), ("ARGMIN", "MIN", "MAX")),
+              ((1, 3, 5, 900000), ("MAX", "ARGMAX", "MIN")), ((1, 1 << 24), ("ARGMIN",)), ((5, 100, 4, 8), ("MIN", "SUM", "MAX")),
+              ((4, 33), ("SUM",)), ((1, 2, 300000), ("ARGMIN", "SUM"))]
+    nests = [(e, ("NONE",) + o, hp.I32) for e, o in shapes]
+    for fill in [None, np.iinfo(np.int32).max, np.iinfo(np.int32).min]:
+        hosts = [workloads.uniform_i32(900 + i, e, -2, 2) if fill is None else np.full(e, fill, np.int32)
+                 for i, (e, _) in enumerate(shapes)]
+        say("case shared folds", fill, flags)
+        for (e, o, _), x, got in zip(nests, hosts, run(nests, hosts, flags)):
+            assert_match(got, x, e, o, what=f"shared folds {e} {o}")
+    x = workloads.normal_f32(950, (1, 1 << 25))
+    nests = [((1, 1 << 25), ("NONE", "SUM"), hp.F32), ((2, 1 << 24), ("NONE", "SUM"), hp.F32), ((7, 9), ("NONE", "SUM"), hp.F32)]
+    hosts = [x, x.reshape(2, -1), x[0, :63].reshape(7, 9).copy()]
+    for (e, o, _), h, got in zip(nests, hosts, run(nests, hosts, flags)):
+        assert_match(got, h, e, o, rel=1e-13, what=f"shared folds {e}")

@@ -89,3 +89,27 @@ def test_tall_stencils_of_one_or_two_strips_keep_their_tiles(probe):
             (1500, 1500, 8), (8192, 8192, 8)]
     got = probe("".join(f"0 {r} {c} {t}\n" for r, c, t in tiles + regs))
     assert [g["reg"] for g in got] == [0] * len(tiles) + [1] * len(regs)
+
+
+def test_no_fold_of_a_batched_nest_is_long(probe):
+    """What unit tasks leave of an output takes its fold a few dozen rounds of memory latency
+    at most; where it would take more the nest runs as its plan's tasks."""
+    nests = LONG_TAILS + [((4, 64, 16, 1024), ("SUM", "ARGMIN", "ARGMAX")), ((1, 345, 131072), ("MIN", "ARGMIN")),
+                          ((1, 89012, 480), ("ARGMAX", "ARGMIN")), ((16, 65536, 2, 128), ("ARGMAX", "ARGMIN", "ARGMAX")),
+                          ((1, 1 << 28), ("SUM",)), ((3, 5, 20, 70), ("SUM", "MAX", "SUM"))]
+    on = 0
+    for (ext, ops), r in zip(nests, probe(nests)):
+        if not r["unit_on"] or not r["folds"]:
+            continue
+        on += 1
+        waves, q = r["fold_waves"], ext[1] if len(ops) == 3 else 1
+        assert waves in (1, 16) and r["folds"] == ext[0]
+        cut = r["lparts"] > 1
+        rows, parts = (ext[-2] if cut and len(ops) > 1 else 1), (r["lparts"] if cut else r["mparts"])
+        up, some, lanes = lambda a, b: -(-a // b), -(-parts // 4), 64 * waves
+        if len(ops) == 3:
+            rounds = [up(q, lanes) * rows * some, up(q, waves) * up(rows, 64) * some, up(q, waves) * rows * up(parts, 256)]
+        else:
+            rounds = [1 << 60, up(rows, lanes) * some, up(rows, waves) * up(parts, 256) if rows > 1 else up(parts, 4 * lanes)]
+        assert rounds[r["fold_form"]] == min(rounds) <= (1 if ext[-1] % 4 == 0 else 4) * (40 if waves > 1 else 4 if ext[0] <= 256 else 32), (ext, r)
+    assert 5 <= on < len(nests)
