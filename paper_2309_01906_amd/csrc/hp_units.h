@@ -52,6 +52,10 @@ struct UnitRoute {
   double unit_bytes; // input bytes of the largest unit, for the order of the tasks
 };
 
+// Tasks of one launch: its threads stay below 2^32, the limit of a grid (a list of more
+// goes out in several launches).
+constexpr int64_t launch_tasks(int64_t threads_per_task) { return ((int64_t)1 << 31) / threads_per_task; }
+
 // What is left of an output -- for eQ iterations of Q, `rows` groups of `parts` carriers
 // (rows: the iterations of M where rows were cut) -- is folded by a wave or, where that
 // would take long, by the kFoldWaves waves of a workgroup.  Each form takes so many rounds

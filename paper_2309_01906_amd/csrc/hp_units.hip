@@ -442,8 +442,8 @@ __global__ void __launch_bounds__(256, kUnitWaves<Raw>) k_units(const UnitDesc* 
 }
 
 template <class Raw>
-__global__ void __launch_bounds__(256, kUnitWaves<Raw>) k_units_of(const UnitDesc* desc, int n) {
-  const int t = (int)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+__global__ void __launch_bounds__(256, kUnitWaves<Raw>) k_units_of(const UnitDesc* desc, int first, int n) {
+  const int t = first + (int)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (t >= n) return;
   unit_any<Raw>(*(const UnitDesc*)((CDesc*)desc), (uint32_t)t, (int)(threadIdx.x & 63));
 }
@@ -587,23 +587,38 @@ hp_status launched() {
   return HP_OK;
 }
 
+
+// `go` for every launch of n tasks: its first task, its tasks and its workgroups.
+template <class Go>
+hp_status in_launches(int64_t n, int64_t tasks_per_group, int64_t threads_per_task, Go go) {
+  const int64_t most = launch_tasks(threads_per_task);
+  hp_status s = HP_OK;
+  for (int64_t t = 0; t < n && s == HP_OK; t += most) {
+    const int64_t k = n - t < most ? n - t : most;
+    go((int)t, (int)k, dim3((unsigned)((k + tasks_per_group - 1) / tasks_per_group)));
+    s = launched();
+  }
+  return s;
+}
+
 }  // namespace
 
 hp_status launch_units(int dtype, const UnitDesc* descs, const int2* tasks, int n, hipStream_t st) {
-  if (n <= 0) return HP_OK;
-  const dim3 grid((unsigned)((n + 3) / 4)), wg(256);
-  if (dtype == HP_F32) hipLaunchKernelGGL(k_units<float>, grid, wg, 0, st, descs, tasks, n);
-  else if (dtype == HP_BF16) hipLaunchKernelGGL(k_units<uint16_t>, grid, wg, 0, st, descs, tasks, n);
-  else hipLaunchKernelGGL(k_units<int32_t>, grid, wg, 0, st, descs, tasks, n);
-  return launched();
+  return in_launches(n, 4, 64, [&](int t, int k, dim3 grid) {
+    const dim3 wg(256);
+    if (dtype == HP_F32) hipLaunchKernelGGL(k_units<float>, grid, wg, 0, st, descs, tasks + t, k);
+    else if (dtype == HP_BF16) hipLaunchKernelGGL(k_units<uint16_t>, grid, wg, 0, st, descs, tasks + t, k);
+    else hipLaunchKernelGGL(k_units<int32_t>, grid, wg, 0, st, descs, tasks + t, k);
+  });
 }
 
 hp_status launch_units_of(int dtype, const UnitDesc* desc, int n, hipStream_t st) {
-  const dim3 grid((unsigned)((n + 3) / 4)), wg(256);
-  if (dtype == HP_F32) hipLaunchKernelGGL(k_units_of<float>, grid, wg, 0, st, desc, n);
-  else if (dtype == HP_BF16) hipLaunchKernelGGL(k_units_of<uint16_t>, grid, wg, 0, st, desc, n);
-  else hipLaunchKernelGGL(k_units_of<int32_t>, grid, wg, 0, st, desc, n);
-  return launched();
+  return in_launches(n, 4, 64, [&](int t, int k, dim3 grid) {
+    const dim3 wg(256);
+    if (dtype == HP_F32) hipLaunchKernelGGL(k_units_of<float>, grid, wg, 0, st, desc, t, t + k);
+    else if (dtype == HP_BF16) hipLaunchKernelGGL(k_units_of<uint16_t>, grid, wg, 0, st, desc, t, t + k);
+    else hipLaunchKernelGGL(k_units_of<int32_t>, grid, wg, 0, st, desc, t, t + k);
+  });
 }
 
 hp_status warm_unit_kernels(hipStream_t st) {
@@ -617,12 +632,13 @@ hp_status warm_unit_kernels(hipStream_t st) {
 }
 
 hp_status launch_unit_folds(const UnitDesc* descs, const int2* tasks, int n_shared, int n, hipStream_t st) {
-  if (n_shared > 0)
-    hipLaunchKernelGGL(k_unit_folds<true>, dim3((unsigned)n_shared), dim3(64 * kFoldWaves), 0, st, descs, tasks, n_shared);
-  if (n > n_shared)
-    hipLaunchKernelGGL(k_unit_folds<false>, dim3((unsigned)((n - n_shared + 3) / 4)), dim3(256), 0, st, descs,
-                       tasks + n_shared, n - n_shared);
-  return n > 0 ? launched() : HP_OK;
+  hp_status s = in_launches(n_shared, 1, 64 * kFoldWaves, [&](int t, int k, dim3 grid) {
+    hipLaunchKernelGGL(k_unit_folds<true>, grid, dim3(64 * kFoldWaves), 0, st, descs, tasks + t, k);
+  });
+  if (s != HP_OK) return s;
+  return in_launches(n - n_shared, 4, 64, [&](int t, int k, dim3 grid) {
+    hipLaunchKernelGGL(k_unit_folds<false>, grid, dim3(256), 0, st, descs, tasks + n_shared + t, k);
+  });
 }
 
 }  // namespace hp

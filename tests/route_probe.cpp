@@ -35,10 +35,11 @@ int main() {
     const hp::UnitRoute u = hp::unit_route(&n, 0, task, false);
     std::printf("seg_kind %d seg_parts %u seg_tail %d tail_parts %u tail_per %d tail_off %llu seg_ws %llu kernel %d "
                 "unit_on %d units %lld folds %lld unit_ws %llu mparts %d lparts %d part_len %d per %d fold_waves %d "
-                "fold_form %d plan_ws %zu\n",
+                "fold_form %d launch_wave %lld launch_group %lld plan_ws %zu\n",
                 s.kind, s.parts, s.tail, s.tail_parts, s.tail_per, (unsigned long long)s.tail_off,
                 (unsigned long long)s.ws_bytes, alone.dp.kernel, u.on, (long long)u.units, (long long)u.folds,
                 (unsigned long long)u.ws_bytes, u.d.mparts, u.d.lparts, u.d.part_len, u.d.per, u.d.fold_waves,
-                u.d.fold_form, task.info.workspace_bytes);
+                u.d.fold_form, (long long)hp::launch_tasks(64),
+                (long long)hp::launch_tasks(64 * hp::kFoldWaves), task.info.workspace_bytes);
   }
 }

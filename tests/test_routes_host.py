@@ -113,3 +113,10 @@ def test_no_fold_of_a_batched_nest_is_long(probe):
             rounds = [1 << 60, up(rows, lanes) * some, up(rows, waves) * up(parts, 256) if rows > 1 else up(parts, 4 * lanes)]
         assert rounds[r["fold_form"]] == min(rounds) <= (1 if ext[-1] % 4 == 0 else 4) * (40 if waves > 1 else 4 if ext[0] <= 256 else 32), (ext, r)
     assert 5 <= on < len(nests)
+
+
+def test_a_launch_of_tasks_stays_below_the_grid_limit(probe):
+    """Lists of tasks go out in launches of fewer than 2^32 threads, whole workgroups each."""
+    r = probe([((2, 3), ("SUM",))])[0]
+    assert r["launch_wave"] * 64 < 1 << 32 and r["launch_wave"] % 4 == 0
+    assert r["launch_group"] * 1024 < 1 << 32
