@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <functional>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -245,20 +246,24 @@ extern "C" hp_status hp_batch_plan(const hp_nest* nests, int64_t n, uint32_t fla
   *out = nullptr;
   if (flags & ~(uint32_t)(HP_BATCH_GRAPH | HP_FLAG_OUT_F32 | HP_BATCH_NO_TUNE))
     return fail(HP_EINVAL, "unknown batch flag bits 0x%x", flags);
-  std::vector<Lowered> plans((size_t)n);
-  std::vector<UnitRoute> routes((size_t)n);
-  const uint32_t pflags = flags & HP_FLAG_OUT_F32;
-  for (int64_t i = 0; i < n; ++i) {
-    bool tuned = false;
-    hp_status s = plan_for_batch(&nests[i], pflags, !(flags & HP_BATCH_NO_TUNE), kBatchWaves, &plans[(size_t)i], &tuned);
-    if (s != HP_OK) {
-      char msg[512];
-      snprintf(msg, sizeof msg, "%s", hp_last_error());
-      return fail(s, "nest %lld: %s", (long long)i, msg);
+  try {
+    std::vector<Lowered> plans((size_t)n);
+    std::vector<UnitRoute> routes((size_t)n);
+    const uint32_t pflags = flags & HP_FLAG_OUT_F32;
+    for (int64_t i = 0; i < n; ++i) {
+      bool tuned = false;
+      hp_status s = plan_for_batch(&nests[i], pflags, !(flags & HP_BATCH_NO_TUNE), kBatchWaves, &plans[(size_t)i], &tuned);
+      if (s != HP_OK) {
+        char msg[512];
+        snprintf(msg, sizeof msg, "%s", hp_last_error());
+        return fail(s, "nest %lld: %s", (long long)i, msg);
+      }
+      routes[(size_t)i] = unit_route(&nests[i], pflags, plans[(size_t)i], tuned);
     }
-    routes[(size_t)i] = unit_route(&nests[i], pflags, plans[(size_t)i], tuned);
+    return batch_from_plans(plans, routes, flags, out);
+  } catch (const std::bad_alloc&) {
+    return fail(HP_ENOMEM, "host allocation failed");
   }
-  return batch_from_plans(plans, routes, flags, out);
 }
 
 extern "C" hp_status hp_batch_plan_inspect(const hp_nest* nests, int64_t n, uint32_t flags, hp_plan_info* infos) {
@@ -277,15 +282,13 @@ extern "C" hp_status hp_batch_plan_inspect(const hp_nest* nests, int64_t n, uint
 hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vector<UnitRoute>& routes, uint32_t flags,
                                hp_batch_s** out) {
   const int64_t n = (int64_t)plans.size();
-  hp_batch_s* b = new (std::nothrow) hp_batch_s;
+  std::unique_ptr<hp_batch_s, void (*)(hp_batch_s*)> own(new (std::nothrow) hp_batch_s, batch_free);
+  hp_batch_s* b = own.get();
   if (!b) return fail(HP_ENOMEM, "host allocation failed");
   b->n = n;
   b->flags = flags;
   b->nw = kBatchWaves;
-  if (hipGetDevice(&b->device) != hipSuccess) {
-    batch_free(b);
-    return fail(HP_EDEVICE, "no HIP device");
-  }
+  if (hipGetDevice(&b->device) != hipSuccess) return fail(HP_EDEVICE, "no HIP device");
   b->plans.resize((size_t)n);
   b->infos.resize((size_t)n);
   for (int64_t i = 0; i < n; ++i) {
@@ -323,15 +326,17 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
     ctr_off[g] = (unit ? 0 : n_ctr++) * kCtrWords * sizeof(unsigned int);
     task_off[g] = arena_bytes;
     arena_bytes = align_up(arena_bytes + (size_t)ntask[g] * sizeof(int2), 256);
-    if (ntask[g] > 0x7fffffffLL) {
-      batch_free(b);
+    if (ntask[g] > 0x7fffffffLL)
       return fail(HP_ETOOBIG, "batch group has %lld tasks, more than 2^31 - 1", ntask[g]);
-    }
   }
   // the descriptors of the nests on unit tasks
   const size_t unit_off = arena_bytes;
   if (b->n_plan_groups < (int)keys.size()) arena_bytes = align_up(arena_bytes + (size_t)n * sizeof(UnitDesc), 256);
+  long long n_unit_fold = 0;
+  for (int64_t i = 0; i < n; ++i) n_unit_fold += routes[(size_t)i].on ? routes[(size_t)i].folds : 0;
+  if (n_unit_fold > 0x7fffffffLL) return fail(HP_ETOOBIG, "batch has %lld fold tasks, more than 2^31 - 1", n_unit_fold);
   std::vector<int2> unit_folds;
+  unit_folds.reserve((size_t)n_unit_fold);
   b->unit_fold_beg.assign((size_t)n, 0);
   for (const int nw : {hp::kFoldWaves, 1}) {  // outputs that a workgroup shares first
     for (int64_t i = 0; i < n; ++i) {
@@ -355,6 +360,7 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   b->n_fold = (int)folds.size();
   const size_t fold_off = arena_bytes;
   arena_bytes = align_up(arena_bytes + folds.size() * sizeof(hp::FoldTask), 256);
+  const size_t head_bytes = arena_bytes;  // what the host fills in; the workspaces follow
   std::vector<size_t> ws_off((size_t)n, 0);
   for (int64_t i = 0; i < n; ++i) {
     const size_t wb = routes[(size_t)i].on ? (size_t)routes[(size_t)i].ws_bytes : b->infos[(size_t)i].workspace_bytes;
@@ -366,12 +372,22 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   if (hipMalloc(&b->d_plans, sizeof(DevPlan) * (size_t)n) != hipSuccess ||
       hipMalloc((void**)&b->d_in, 3 * sizeof(void*) * (size_t)n) != hipSuccess ||
       hipMalloc(&b->arena, arena_bytes) != hipSuccess) {
-    batch_free(b);
+    (void)hipGetLastError();
+    own.reset();
+    // without the nests whose carriers take more than their plan's partials, as plan tasks
+    std::vector<UnitRoute> lean(routes);
+    bool less = false;
+    for (int64_t i = 0; i < n; ++i)
+      if (lean[(size_t)i].on && lean[(size_t)i].ws_bytes > plans[(size_t)i].info.workspace_bytes) {
+        lean[(size_t)i].on = 0;
+        less = true;
+      }
+    if (less) return batch_from_plans(plans, lean, flags, out);
     return fail(HP_ENOMEM, "batch device allocation failed");
   }
   b->d_out = reinterpret_cast<void**>(const_cast<void**>(b->d_in + n));
   b->d_ws = reinterpret_cast<unsigned char**>(const_cast<void**>(b->d_in + 2 * n));
-  std::vector<unsigned char> host_arena(arena_bytes, 0);
+  std::vector<unsigned char> host_arena(head_bytes, 0);
   b->d_units = reinterpret_cast<UnitDesc*>((unsigned char*)b->arena + unit_off);
   b->d_unit_folds = reinterpret_cast<int2*>((unsigned char*)b->arena + unit_fold_off);
   if (!unit_folds.empty()) memcpy(host_arena.data() + unit_fold_off, unit_folds.data(), unit_folds.size() * sizeof(int2));
@@ -443,13 +459,11 @@ hp_status hp::batch_from_plans(const std::vector<Lowered>& plans, const std::vec
   }
   std::vector<unsigned char*> wsv(b->ws_ptrs);
   if (hipMemcpy(b->d_plans, b->plans.data(), sizeof(DevPlan) * (size_t)n, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->arena, host_arena.data(), arena_bytes, hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(b->arena, host_arena.data(), head_bytes, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(b->d_ws, wsv.data(), sizeof(void*) * (size_t)n, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(b->d_in, 0, 2 * sizeof(void*) * (size_t)n) != hipSuccess) {
-    batch_free(b);
+      hipMemset(b->d_in, 0, 2 * sizeof(void*) * (size_t)n) != hipSuccess)
     return fail(HP_EDEVICE, "batch upload failed");
-  }
-  *out = b;
+  *out = own.release();
   return HP_OK;
 }
 

@@ -162,6 +162,10 @@ UnitRoute unit_route(const hp_nest* n, uint32_t flags, const Lowered& L, bool tu
     // carriers of 16 bytes must stay well below the input they stand for, or be few
     if (carriers && pair_bytes < 32 && carriers > (1 << 18)) return off;
   }
+  // Device memory that the plan's tasks do without, with the fold tasks: up to 64 MiB, or a
+  // sixteenth of the input (1048576 x 64 x 4 x 2, 2 GiB, would keep another GiB).
+  const int64_t kept = carriers * kSlotBytes + (carriers ? n_out * 8 : 0), some = (int64_t)(L.info.in_bytes / 16);
+  if (kept > 64 << 20 && kept > some && kept > (int64_t)L.info.workspace_bytes) return off;
   D.partial = carriers ? 1 : 0;
   D.fold_waves = 1;
   if (carriers) {

@@ -120,3 +120,17 @@ def test_a_launch_of_tasks_stays_below_the_grid_limit(probe):
     r = probe([((2, 3), ("SUM",))])[0]
     assert r["launch_wave"] * 64 < 1 << 32 and r["launch_wave"] % 4 == 0
     assert r["launch_group"] * 1024 < 1 << 32
+
+
+def test_batched_nests_keep_little_memory(probe):
+    """Unit tasks keep at most a sixteenth of a nest's input on the device beside it, or 64
+    MiB, or what the plan's tasks would keep."""
+    nests = [((1048576, 64, 4, 2), ("SUM", "MAX", "SUM")), ((67108864, 2, 2, 4), ("SUM", "MAX", "SUM")),
+             ((1048576, 64, 8, 32), ("MIN", "SUM", "ARGMAX")), ((1000000, 3, 40, 7), ("SUM", "MAX", "SUM")),
+             ((4096, 256, 16, 16), ("SUM", "MAX", "SUM")), ((1 << 22, 4, 2, 8), ("SUM", "MAX", "SUM"))]
+    on = []
+    for (ext, ops), r in zip(nests, probe(nests)):
+        kept = r["unit_ws"] + 8 * r["folds"]
+        assert not r["unit_on"] or kept <= max(64 << 20, math.prod(ext) * 4 // 16, r["plan_ws"]), (ext, r)
+        on.append(r["unit_on"])
+    assert on == [0, 0, 1, 1, 1, 0]  # the third keeps 1 GiB beside 64
