@@ -1031,8 +1031,12 @@ static void split_tail(SegRoute& S, int64_t n) {
 // drawn through 2,200 nests of even levels up to 64 MiB: of the 288 that had got more than 5 %
 // slower 221 are ended as before, and 36 lose more than 0.3 us, at most 32 %.
 static bool chain_ends_sooner(const SegRoute& S, const Lowered& L, int64_t pairs) {
-  if (L.dp.kernel != HP_KERNEL_INT_CHAIN || L.dp.gsplit != 1) return false;
+  if (L.dp.kernel != HP_KERNEL_INT_CHAIN) return false;
   const int64_t strips = L.dp.outer_iters, pair = (int64_t)S.eL * S.eM, bytes = 4 * pairs * pair, n = S.n_out;
+  // beyond the last-level cache the chain kernel streams rows of whole lines at the rate of
+  // memory, runs of short pairs do not (2048 x 256 x 2 x 64: 60.7 us, 75.0 in runs)
+  if (bytes >= 128 << 20 && S.eL >= 64 && pair <= 256) return true;
+  if (L.dp.gsplit != 1) return false;
   if (strips == 1 && pair <= 256 && (n <= 1024 || L.dp.nw < 4) && (n <= 8192 || pairs > 1 << 17)) return true;
   if (strips <= 2 && pair <= 256 && pairs > 4096 && bytes <= 8 << 20) return true;  // a load or two per wave there
   if (strips <= 2 && pair <= 64 && pairs > 1 << 18) return true;                    // carriers of 16 bytes per 256
@@ -1143,6 +1147,14 @@ SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   S.waves = nw > 4 ? 8 : nw > 1 ? 4 : 1;
   int64_t parts = nw / 8 < 1 ? 1 : nw / 8;
   if (parts > 1 && small && parts > cdiv(pair_bytes, 8 * 4096)) parts = cdiv(pair_bytes, 8 * 4096);
+  // A few large pairs in parts do not reach the rate of memory that the chain kernel's
+  // workgroups do beyond the last-level cache (4 x 65536 x 256 MIN, SUM: 50.4 us, 61.1 in
+  // parts; at half of it parts are the faster ones).
+  if (parts > 1 && ns == 2 && L.dp.kernel == HP_KERNEL_INT_CHAIN && S.eL >= 64 && S.eL <= 768 && pairs * pair_bytes >= 256 << 20)
+    return off;
+  // two parts and a tail take longer than eight waves alone where those fill a quarter of
+  // the chip (512 x 128 x 128 MIN, SUM: 13.0 us in parts, 9.5 without, 11.0 by the chain kernel)
+  if (parts == 2 && ns == 2 && small && pairs >= 256) parts = 1;
   const int64_t per = cdiv(steps, parts);
   parts = cdiv(steps, per);
   S.per = (int32_t)per;

@@ -134,3 +134,17 @@ def test_batched_nests_keep_little_memory(probe):
         assert not r["unit_on"] or kept <= max(64 << 20, math.prod(ext) * 4 // 16, r["plan_ws"]), (ext, r)
         on.append(r["unit_on"])
     assert on == [0, 0, 1, 1, 1, 0]  # the third keeps 1 GiB beside 64
+
+
+def test_chains_beyond_the_last_level_cache_stay_with_the_chain_kernel(probe):
+    """Even nests of 256 MiB and more in a few pairs, or of 128 MiB and more in short pairs of
+    whole lines; smaller ones, other rows and many pairs take the segment kernels.  Pairs of
+    64 KiB that fill a quarter of the chip are not cut in two."""
+    two, three = ("MIN", "SUM"), ("MIN", "ARGMAX", "MAX")
+    cases = [((4, 65536, 256), two, 0), ((512, 1024, 128), two, 0), ((4, 32768, 256), two, 1), ((4, 65536, 255), two, 1),
+             ((1 << 16, 8, 128), two, 1), ((4096, 256, 2, 64), three, 0), ((8, 32768, 4, 64), three, 0),
+             ((64, 8192, 4, 32), three, 1), ((64, 1024, 4, 64), three, 1)]
+    for (ext, ops, kind), r in zip(cases, probe([c[:2] for c in cases])):
+        assert r["seg_kind"] == kind, (ext, r)
+    for r in probe([((512, 128, 128), two), ((300, 100, 163), two)]):
+        assert r["seg_parts"] == 1 and r["seg_tail"] == 0
