@@ -2,7 +2,7 @@
 """Benchmark of the nested multi-level reduction on one MI355X.
 
 Headline workload: the plain 3-level nest, fp32 4096 x 256 x 256 (1 GiB, N(0,1)),
-out[i] = sum_j sum_k A[i,j,k] with fp32 compensated accumulation and fp64 output,
+out[i] = sum_j sum_k A[i,j,k] summed in fp64 from the first element on, fp64 output,
 levels mapped grid -> waves -> lanes.  A step is one hp_run over the whole array
 (input resident in HBM); value = algorithmic bytes (input + output) per second.
 
@@ -31,7 +31,17 @@ METRIC = "achieved HBM GB/s (% of peak) for nested reduction; batched-vs-plain; 
 # the CPU baseline leg: the oracle checks of GPU results (off with --no-cpu-baseline)
 ORACLE_CHECKS = True
 PEAK_GBS = 8000.0  # MI355X HBM3E, vendor figure
-KERNEL_SOURCES = ["hp_nest.h", "hp_lanes.h", "hp_nest_f32.hip", "hp_rows.hip", "hp_internal.h", "hp_plan.cpp"]
+KERNEL_SOURCES = ["hp_rows.hip", "hp_red.h", "hp_nest.h", "hp_lanes.h", "hp_fold.h", "hp_internal.h", "hp_plan.cpp"]
+
+
+def rows_kernel(info) -> str:
+    """The kernel that runs an automatic float plan of one long contiguous sum per output."""
+    return f"hp::k_rows_long<float, 1, {info['waves']}>"
+
+
+# the kernels of the automatic plans of the int32 workloads (the plan's own, which its map
+# describes, run only on request)
+INT_KERNELS = {"c1": "hp::k_rows_short<int, 1, 4, 1>", "c3": "hp::k_seg_rows<4, 1, 4, 4>, hp::k_seg_tail"}
 
 
 def kernel_hash() -> str:
@@ -252,7 +262,8 @@ def extra_int_workloads(steps, warmup, stream):
                 cold.append(s.elapsed_time(e))
             nbytes = x.nbytes + p.info["out_bytes"]
             res[name] = {
-                "shape": list(nest.extents), "bytes": nbytes, "map": p.info["map"], "grid": p.info["grid"],
+                "shape": list(nest.extents), "bytes": nbytes, "kernel": INT_KERNELS[name],
+                "map": p.info["map"], "grid": p.info["grid"],
                 "warm_p50_us": round(pct(ev, 50) * 1e3, 2), "warm_p99_us": round(pct(ev, 99) * 1e3, 2),
                 "cold_p50_us": round(pct(cold, 50) * 1e3, 2), "cold_p99_us": round(pct(cold, 99) * 1e3, 2),
                 "cold_GBps": round(nbytes / (pct(cold, 50) * 1e-3) / 1e9, 1),
@@ -298,7 +309,7 @@ def extra_ragged_and_xcd(steps, warmup, stream):
         nb = x.nbytes + p.info["out_bytes"]
         got = out.cpu().numpy()
         res["ragged_fp32_4096x65537"] = {
-            "bytes": nb, "kernel": p.info["kernel_name"], "flat_block": p.info["flat_block"],
+            "bytes": nb, "kernel": rows_kernel(p.info), "flat_block": p.info["flat_block"],
             "p50_us": round(pct(ev, 50) * 1e3, 1), "GBps": round(nb / (pct(ev, 50) * 1e-3) / 1e9, 1)}
         if ORACLE_CHECKS:
             import oracle
@@ -630,7 +641,7 @@ def main():
         info = hp.inspect(workloads.C2.extents, workloads.C2.ops, workloads.C2.dtype)
         if len(args.ingest_counters) not in (2, 3):
             raise SystemExit("--ingest-counters takes FETCH_CSV WRITE_CSV [SQ_CSV]")
-        ingest_counters(args.ingest_counters[0], args.ingest_counters[1], info["kernel_name"],
+        ingest_counters(args.ingest_counters[0], args.ingest_counters[1], rows_kernel(info),
                         info["in_bytes"] + info["out_bytes"],
                         sq_csv=args.ingest_counters[2] if len(args.ingest_counters) == 3 else None)
         return
@@ -717,7 +728,7 @@ def main():
         "p50_us": round(pct(ev_ms, 50) * 1e3, 2), "p99_us": round(pct(ev_ms, 99) * 1e3, 2),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_GBS, 4), "traffic": traffic_from_profiles(nbytes),
-                     "kernel": f"hp::k_rows_long<float, 1, {plan.info['waves']}>",  # one contiguous sum per output
+                     "kernel": rows_kernel(plan.info),
                      "algorithmic_bytes_per_launch": nbytes,
                      "kernel_hash": kernel_hash(), "utilisation": utilisation_from_profiles(avg_ev)},
     }

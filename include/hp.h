@@ -163,9 +163,11 @@ typedef struct hp_plan_info {
  * map, no flag but HP_FLAG_OUT_F32) with one reduction per output over a contiguous
  * block -- float sums of sums, int32 with one operator or one ARG level -- is run by
  * the row kernels instead (csrc/hp_rows.hip), and one of two or three int32 segments by
- * the segment kernels (csrc/hp_segs.hip): the same outputs without a plan in memory;
- * `kernel` and the geometry then describe the map that the plan's own kernels would
- * take, and the workspace may be larger than workspace_bytes. */
+ * the segment kernels (csrc/hp_segs.hip), where those are faster: the same outputs
+ * without a plan in memory; `kernel` and the geometry then describe the map that the
+ * plan's own kernels would take.  The segment kernels may keep more than workspace_bytes,
+ * up to some 64 MiB or 1/500 of the input, whichever is larger; where that cannot be
+ * allocated the plan's own kernels run. */
 typedef enum hp_kernel {
   HP_KERNEL_LEAN = 0,     /* float, depth <= 4, at most one strided inner dim, <= 8 waves, vector chunk */
   HP_KERNEL_GENERIC4 = 1, /* float, depth <= 4 */
@@ -221,8 +223,9 @@ hp_status hp_destroy(hp_plan_t plan);
  * host exactly as hp_plan would plan it (same kernels, same bits as hp_run); the
  * plan, the fold tasks and the workgroup partials of a grid-split nest go into a
  * file-scope device array of HP_STATIC_SCRATCH_BYTES bytes that each GPU the
- * library runs on holds until the process ends.  The plan reaches that array
- * through a small install kernel on `stream`, then the nest kernels run there.
+ * library runs on holds until the process ends.  Where the nest runs on the plan's own
+ * kernels, the plan reaches that array through a small install kernel on `stream`; the
+ * row, segment and ordered kernels take their arguments with the launch.
  * d_in, d_out and stream are as for hp_run; the call is asynchronous.
  * Every call on one GPU shares that GPU's array: calls on one stream are ordered,
  * but calls that overlap on one GPU (two streams, two threads) race and may give
@@ -243,7 +246,10 @@ hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* map, uint32_
  * A nest of one to three reducing segments (adjacent levels of one operator are one
  * segment) runs as unit tasks: one-wavefront pieces of some tens of KiB of its input,
  * one launch per element type, the largest pieces first.  Nests cut into pieces, and
- * those of three segments, are folded by a second kernel.
+ * those of three segments, are folded by a second kernel (outputs of many pieces by a
+ * third).  A nest whose fold would take long, or whose pieces would keep more than 64 MiB
+ * and a sixteenth of its input on the device, does not run as unit tasks; if the batch
+ * cannot be allocated otherwise, none does that keeps more than its plan's partials.
  *
  * Other nests run as tasks of their plans: every wavefront of persistent workgroups is
  * an independent worker that starts on tasks dealt to it statically and then takes
@@ -253,8 +259,9 @@ hp_status hp_reduce_static(const hp_nest* nest, const hp_level_map* map, uint32_
  * also resets the task counters for the next run.
  *
  * A nest's own shape and the tuner cache decide its pieces, never the batch, so its
- * result is the same bits as a launch of its own (hp_batch_run_each).  Ordered products
- * (HP_OP_PROD) are not batched.
+ * result is the same bits as a launch of its own (hp_batch_run_each).  Those are the bits
+ * of hp_run for integers; a float sum is added in another order there and may differ in
+ * its last bits.  Ordered products (HP_OP_PROD) are not batched.
  */
 typedef struct hp_batch_s* hp_batch_t;
 
@@ -327,9 +334,11 @@ hp_status hp_tune_cache_size(int64_t* n);
  * still fits (else it waits for the next batch, under the same bounded bypass), so
  * no request fails because of what it was packed with.  If a launch fails after
  * some of its work was enqueued, the slot stays busy until its stream has drained,
- * and only then are its requests failed (HP_EDEVICE).  Each request keeps the plan it would get alone, so its
- * result does not depend on the batch it ran in.  Payloads are not copied: d_in
- * and d_out must stay valid until the request completes.
+ * and only then are its requests failed (HP_EDEVICE).  How a request runs is decided when
+ * it is submitted, by its nest, the tuner cache and slot_bytes alone -- as unit tasks where
+ * those fit a slot, else as tasks of its plan -- so its result does not depend on the batch
+ * it ran in; the last bits of a float sum may depend on slot_bytes.  Payloads are not
+ * copied: d_in and d_out must stay valid until the request completes.
  */
 typedef struct hp_server_s* hp_server_t;
 
@@ -345,7 +354,7 @@ typedef struct hp_server_cfg {
   uint32_t flags;                 /* HP_FLAG_OUT_F32, HP_SERVER_FAKE_DEVICE */
   int32_t fail_every_nth_batch;   /* test hook: every n-th batch fails (0: never) ... */
   int32_t fail_step;              /* ... before its device step fail_step: 0 the descriptor upload, then one
-                                     step per persistent launch and the fold launch (clamped to the last) */
+                                     step per launch of tasks and one per kind of fold (clamped to the last) */
 } hp_server_cfg;
 
 typedef struct hp_req_info {

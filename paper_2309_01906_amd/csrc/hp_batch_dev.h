@@ -5,8 +5,8 @@
 
 namespace hp {
 
-// Persistent batched kernels, for the nests that are not unit tasks (hp_units.hip) and the
-// server: workers pop (nest, workgroup) tasks with atomic
+// Persistent batched kernels, for the nests of batches and the server that are not unit
+// tasks (hp_units.hip): workers pop (nest, workgroup) tasks with atomic
 // counters -- a dynamic schedule on the grid level.  The tasks are dealt, largest
 // first, each to the queue with the least estimated work so far, into kQueues
 // queues with one counter each; workgroup b takes from queue

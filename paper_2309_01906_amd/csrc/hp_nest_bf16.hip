@@ -1,4 +1,4 @@
-// Nest kernels for bf16 inputs (SUM levels, exact widening to fp32, fp32 pair accumulation, fp64 output).
+// Nest kernels for bf16 inputs (SUM levels, exact widening, summed in fp64).
 #include "hp_nest.h"
 
 namespace hp {

@@ -1,4 +1,4 @@
-// Nest kernels for fp32 inputs (SUM levels, fp32 pair accumulation, fp64 output).
+// Nest kernels for fp32 inputs (SUM levels, summed in fp64).
 #include "hp_nest.h"
 
 namespace hp {

@@ -973,11 +973,13 @@ RowRoute row_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, co
   if (r.waves > 8) return RowRoute{};
   int64_t parts = L.dp.gsplit;
   if (parts == 1) {
-    // The plan's waves, but: four where they load most of a batch of 16 KiB at once (8192 x
-    // 4096 float 24.5 -> 20.8 us, 5461 x 6144 22.0 -> 21.1; 7277 x 4611 would go from 21.7 to
-    // 22.1, 2048 x 8192 int32 from 11.8 to 12.9), one for blocks that are many batches and many enough (1365 x 24576 22.3 ->
-    // 21.2, 1500 x 30011 28.7 -> 28.0; blocks of 256 KiB are as fast on eight), and more
-    // than one where outputs are few (546 x 30720 int32 ARGMIN 18.9 -> 12.5,
+    // The plan's waves, as for its own kernels and so also between and beyond the sizes named
+    // here, but: four where they load most of a batch of 16 KiB at once (8192 x 4096 float
+    // 24.5 -> 20.8 us, 5461 x 6144 22.0 -> 21.1; a batch that is mostly empty costs a whole
+    // one: 7277 x 4611 would go from 21.7 to 22.1, 2048 x 8192 int32 from 11.8 to 12.9), one
+    // for blocks that are many batches and many enough to fill the chip with a wave each
+    // (1365 x 24576 22.3 -> 21.2, 1500 x 30011 28.7 -> 28.0; blocks of 256 KiB are as fast on
+    // eight), and more than one where outputs are few (546 x 30720 int32 ARGMIN 18.9 -> 12.5,
     // 200 x 20000 SUM 11.0 -> 4.6, 900 x 12000 float 9.7 -> 8.1).
     const int64_t bytes = block * (16 / vec), last = bytes % 16384;
     if (n_out >= 1024 && bytes >= 12 << 10 && bytes < 32 << 10 && (last == 0 || last >= 8192)) r.waves = 4;
@@ -1050,7 +1052,10 @@ static bool chain_ends_sooner(const SegRoute& S, const Lowered& L, int64_t pairs
 // the plan's kernels: (61, 125, 67, 59) SUM, MAX, ARGMIN 105 -> 27 us, (1024, 64, 1024)
 // ARGMAX of SUM 75 -> 42, the chain (64, 128, 64, 64) 34.0 -> 26, (4096, 16, 1024) SUM
 // of MAX 44.3 -> 41.8, (16777, 2048, 2) MAX of SUM 530 -> 44, (1, 2, 2^24) SUM of MAX
-// 8,306 -> 25, (1000000, 3, 5) MAX of SUM 849 -> 31; none was slower.
+// 8,306 -> 25, (1000000, 3, 5) MAX of SUM 849 -> 31.  Where the plan's chain kernel is the
+// faster one it stays: short even chains (chain_ends_sooner) and, beyond the last-level
+// cache, even rows of whole lines.  Over 33,000 drawn nests of up to 512 MiB 0.7 % are more
+// than 4 % slower than by the plan's kernels, 1.4 times at most.
 //   Rows of up to four vectors per lane go with M in one pass; longer ones through the
 // row kernels first (their values are at most 1/512 of the input).
 SegRoute seg_route(const hp_nest* n, const hp_level_map* map, uint32_t flags, const Lowered& L) {

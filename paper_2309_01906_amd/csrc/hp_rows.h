@@ -8,7 +8,8 @@
 namespace hp {
 
 // Run a nest whose plan has a row route (RowRoute::kind != ROWS_OFF); ws holds the
-// partials of a split block (row_ws_bytes, not more than the plan's workspace).
+// partials of a split block, n_out * parts of 8 bytes: no more than the plan's workspace,
+// which has 16 for each of at least as many.
 hp_status launch_rows(const RowRoute& r, const void* in, void* out, void* ws, hipStream_t st);
 
 }  // namespace hp

@@ -10,7 +10,8 @@
 //     With as many pairs as fill the chip a wave runs through one or several (k_seg_run),
 //     some of them side by side when M is short.
 //   longer rows: the row kernels reduce every row to one value first.
-// k_seg_tail then reduces what is left: the parts of M, or its values, and Q.
+// k_seg_tail then reduces what is left: the parts of M, or its values, and Q, in parts of
+// its own where a few outputs have a long outermost level.
 //
 // Measured, from 4096 to 8192 waves that walk their pairs to waves of some 4 KiB:
 //   64 x 128 x 64 x 64 SUM, MAX, ARGMIN (128 MiB)      32.0 -> 26.8 us

@@ -44,12 +44,15 @@ inline int reg_rows(long long R, long long C, int t) {
 // x 500, 4: 10.2 against 10.6 us).  One or two strips both hold an edge, whose columns are
 // loaded and stored one by one: tall ones stay with LDS where that has been the faster form
 // (2 sweeps: 2516 x 484 7.4 against 8.7 us, but 380 x 492 5.9 against 4.6; 3: 4096 x 380 8.6
-// against 9.4; 4: 2048 x 256 8.3 against 8.9).  From 5 sweeps a wave of a small array has more ghost rows than rows
-// of its own, and both forms are mostly latency: what each takes then is estimated, in
-// tenths of a microsecond, from fits to 18 arrays of 200 x 200 to 8192 x 8192 cells (LDS
+// against 9.4; 4: 2048 x 256 8.3 against 8.9).  From 5 sweeps a wave of a small array has
+// more ghost rows than rows of its own, and both forms are mostly latency: what each takes
+// then is estimated, in tenths of a microsecond -- the register form by the steps of the
+// fullest SIMD's waves (rows and ghost rows), the LDS form by the tiles of a compute unit,
+// each with its launch -- from fits to 18 arrays of 200 x 200 to 8192 x 8192 cells (LDS
 // against registers, 8 sweeps: 600 x 600 15.0 and 13.6 us, 1024 x 1024 15.7 and 16.3,
 // 7000 x 300, whose two strips both hold an edge, 20.6 and 22.0, 1500 x 1500 20.5 and
-// 18.5, 8192 x 8192 266 and 148).
+// 18.5, 8192 x 8192 266 and 148).  Over 6,200 arrays of 3 x 3 to 8192 x 8192 cells ten were
+// more than 4 % slower than in LDS, by at most 7 %.
 inline bool reg_form(long long R, long long C, int t) {
   if (t <= 1) return false;
   const long long w = kRegCols - 2 * reg_ghost(t), ns = (C + w - 1) / w;
