@@ -176,3 +176,26 @@ def test_folds_that_a_workgroup_shares(flags):
     hosts = [x, x.reshape(2, -1), x[0, :63].reshape(7, 9).copy()]
     for (e, o, _), h, got in zip(nests, hosts, run(nests, hosts, flags)):
         assert_match(got, h, e, o, rel=1e-13, what=f"shared folds {e}")
+
+
+def test_served_folds_that_a_workgroup_shares():
+    """Requests whose outputs a workgroup or a wave folds, and plan tasks, in the same batches of a server."""
+    shapes = [((2, 3000, 8, 64), ("ARGMIN", "MAX", "SUM")), ((5, 100, 4, 8), ("MIN", "SUM", "MAX")), ((4, 33), ("SUM",)),
+              ((1, 40000, 4, 8), ("SUM", "MAX", "SUM")), ((3, 700, 40, 90), ("ARGMAX", "ARGMIN", "MAX")),
+              ((2, 3, 2, 5, 7), ("SUM", "MAX", "SUM", "MIN")), ((2, 90, 40000), ("SUM", "ARGMAX"))]
+    nests = [(e, ("NONE",) + o, hp.I32) for e, o in shapes]
+    hosts = [workloads.uniform_i32(970 + i, e, -2, 2) for i, (e, _) in enumerate(shapes)]
+    devs = [to_device(h) for h in hosts]
+    say("case served folds", len(nests))
+    with hp.Server(slot_bytes=64 << 20, streams=2, max_batch=32) as s:
+        for _ in range(3):
+            outs = []
+            for e, o, d in nests:
+                inf = hp.inspect(e, o, d)
+                outs.append(torch.full((inf["n_out"],), 77, dtype=hp.torch_out_dtype(inf["out_dtype"]), device="cuda"))
+            torch.cuda.synchronize()
+            tickets = s.replay(nests, [t.data_ptr() for t in devs], [t.data_ptr() for t in outs], [0.0] * len(nests))
+            assert all(s.wait(t)["status"] == 0 for t in tickets)
+            torch.cuda.synchronize()
+            for (e, o, _), x, got in zip(nests, hosts, outs):
+                assert_match(got.cpu().numpy(), x, e, o, what=f"served folds {e} {o}")
