@@ -137,10 +137,11 @@ def ingest_counters(fetch_csv, write_csv, kernel, nbytes, copy_bytes=1 << 30, sq
                     out.append((r["Kernel_Name"], int(r["Grid_Size"]), float(r["Counter_Value"])))
         return out
 
+    base = kernel.split("::")[-1]  # the profiler writes unnamed namespaces too
     res = {}
     for counter, path in (("FETCH_SIZE", fetch_csv), ("WRITE_SIZE", write_csv)):
         rs = rows(path, counter)
-        ks = [v for n, _, v in rs if kernel in n]
+        ks = [v for n, _, v in rs if base in n]
         copies = [(g, v) for n, g, v in rs if "copyBuffer" in n]
         if not ks or not copies:
             raise SystemExit(f"{path}: no {counter} rows for {kernel} or for the calibration copy")
@@ -157,7 +158,7 @@ def ingest_counters(fetch_csv, write_csv, kernel, nbytes, copy_bytes=1 << 30, sq
         sums, n = {}, {}
         with open(sq_csv) as fh:
             for r in csv.DictReader(fh):
-                if kernel in r["Kernel_Name"]:
+                if base in r["Kernel_Name"]:
                     c = r["Counter_Name"]
                     sums[c] = sums.get(c, 0.0) + float(r["Counter_Value"])
                     n[c] = n.get(c, 0) + 1
