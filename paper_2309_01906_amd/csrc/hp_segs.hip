@@ -432,7 +432,10 @@ __global__ void __launch_bounds__(256) k_seg_tail_lane(const In* __restrict__ ws
 template <class In, bool PARTS>
 void tail(const SegRoute& S, int n, const In* ws, void* out, unsigned char* base, hipStream_t st) {
   const long long per = (long long)S.eQ * n;
-  if (per <= 64 && S.n_out >= 4096) {
+  // A lane walks its output's entries one after the other, so that takes as long for a few
+  // outputs as for many: 4096 x 21 x 1 x 4 MAX, ARGMAX, ARGMIN 17.1 us, 11.0 by the plan's
+  // kernels, 8.9 with a workgroup per output (18123 x 9 x 8 x 2: 14.2 us by lanes, 17.0 so).
+  if (per <= 64 && S.n_out >= 4096 && (per <= 8 || per * 1400 <= S.n_out)) {
     hipLaunchKernelGGL((k_seg_tail_lane<In, PARTS>), dim3((unsigned)((S.n_out + 255) / 256)), dim3(256), 0, st, ws, out,
                        (long long)S.n_out, S.eQ, n, S.opQ, S.opM, S.out64);
     return;

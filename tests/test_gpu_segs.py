@@ -149,3 +149,10 @@ def test_short_even_chains(ops):
     for ext in [(512, 8, 4, 8), (16, 4, 16, 4), (265, 128, 2, 16), (6516, 32, 4, 4), (3183, 64, 2, 4), (1, 32, 2, 16),
                 (102, 4, 2, 256), (512, 512, 8, 4), (9000, 2, 8, 8), (1030, 8, 4, 64)]:
         check(ext, ("NONE",) + ops, -3, 3, 370)
+
+
+@pytest.mark.parametrize("ext", [(4096, 21, 1, 4), (4096, 8, 2, 5), (4097, 9, 3, 5), (11300, 8, 2, 3), (12600, 9, 1, 7), (12599, 9, 1, 7)])
+def test_tails_of_many_outputs(ext):
+    """Tails by a lane and by a workgroup per output, on both sides of the line."""
+    for ops in THREE:
+        check(ext, ("NONE",) + ops, -2, 2, 380)
